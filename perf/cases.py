@@ -6,16 +6,16 @@ A serving process calls the library in three ways, and each has its cases:
     ``vsk_decode_step_scratch``, ``vsk_decode_step_routed``), alone or as the
     serving loop's batch_build + batch_upload + step;
   * ``chunk``: prompt rows, alone or beside decoding sequences
-    (``vsk_prefill_chunk``, ``vsk_prefill_chunk_routed``), optionally followed
-    by reading the new KV out (``vsk_kv_read``), as a prefill worker does that
-    hands a prompt over to a decode worker;
+    (``vsk_prefill_chunk``, ``vsk_prefill_chunk_routed``), followed by reading
+    the new KV out (``vsk_kv_read``);
   * ``sample``: ``vsk_argmax_sample`` over given logits.
 
 Most cases are a few layers of a model at its real widths with its real
 head, so that a change of rounding in one layer stays visible in the logits;
 one is a whole model.  Every decode row and every chosen prompt row returns
-its logits, and passes over a few layers return the KV pool as well (new K
-and V of every row of every layer).  The greedy ids are computed by each pass
+its logits, and passes that hand their new KV on (``read_kv``: a prefill
+worker's, a server's that copies its cache to another store) return the new K
+and V of every row of every layer.  The greedy ids are computed by each pass
 but not compared: they follow from the logits, and two logits closer than
 bf16 resolves may swap.
 """
@@ -38,12 +38,13 @@ VOCAB = 128256
 
 
 # ------------------------------------------------------------------ cases
-def _decode(name, model, layers, rows, lo, hi, vocab=VOCAB, prefix=0, groups=0, api="step", spread="uniform", skip=0.0):
+def _decode(name, model, layers, rows, lo, hi, vocab=VOCAB, prefix=0, groups=0, api="step", spread="uniform",
+            skip=0.0, read_kv=False):
     return dict(name=name, kind="decode", model=model, layers=layers, vocab=vocab, rows=rows, lo=lo, hi=hi,
-                prefix=prefix, groups=groups, api=api, spread=spread, skip=skip)
+                prefix=prefix, groups=groups, api=api, spread=spread, skip=skip, read_kv=read_kv)
 
 
-def _chunk(name, model, layers, prompts, plen, past, decodes, lo, hi, vocab=VOCAB, read_kv=False, skip=0.0):
+def _chunk(name, model, layers, prompts, plen, past, decodes, lo, hi, vocab=VOCAB, read_kv=True, skip=0.0):
     return dict(name=name, kind="chunk", model=model, layers=layers, vocab=vocab, prompts=prompts, plen=plen,
                 past=past, rows=decodes, lo=lo, hi=hi, read_kv=read_kv, skip=skip)
 
@@ -60,16 +61,16 @@ def listed():
         # a common few-shot prompt held once, 64 sequences behind it
         _decode("prefix_3b_b64", "3B", 4, 64, 50, 150, prefix=1536, groups=1),
         # an odd batch between the tile sizes, contexts from short to long
-        _decode("odd_8b_b37", "8B", 4, 37, 100, 6000, vocab=32000),
+        _decode("odd_8b_b37", "8B", 4, 37, 100, 6000, vocab=32000, read_kv=True),
         # a full server: heavy-tailed contexts
         _decode("serve_8b_b128", "8B", 4, 128, 16, 4096, spread="lognormal"),
         # routed decode where routing pays: many resident tokens, half of the
         # routed decisions Project-Only
-        _decode("routed_8b_b256", "8B", 4, 256, 600, 1400, skip=0.5),
+        _decode("routed_8b_b256", "8B", 4, 256, 600, 1400, skip=0.5, read_kv=True),
         # chunked prefill beside decoding sequences
         _chunk("mixed_3b_2080", "3B", 4, 4, 512, 0, 32, 256, 2048),
         # one prompt of an odd length whose KV is then handed over
-        _chunk("prompt_8b_777_kv", "8B", 2, 1, 777, 0, 0, 0, 0, vocab=32000, read_kv=True),
+        _chunk("prompt_8b_777_kv", "8B", 2, 1, 777, 0, 0, 0, 0, vocab=32000),
         # a later chunk of a long document, a few decodes beside it
         _chunk("later_chunk_3b_1000", "3B", 4, 1, 1000, 4104, 7, 300, 3000),
         # routed prefill of a few shorter prompts
@@ -108,7 +109,7 @@ def _draw_one(rng):
         if rows <= 16 and kind == "decode" and rng.random() < 0.4:
             api = "scratch"
         c = _decode("", model, layers, rows, lo, hi, vocab, prefix, groups, api, rng.choice(["uniform", "lognormal"]),
-                    round(rng.uniform(0.1, 0.9), 2) if kind == "routed" else 0.0)
+                    round(rng.uniform(0.1, 0.9), 2) if kind == "routed" else 0.0, rng.random() < 0.4)
     else:
         prompts = rng.randint(1, 5)
         plen = _log(rng, 17, 2048)
@@ -116,7 +117,7 @@ def _draw_one(rng):
         dec = _log(rng, 1, 64) if kind == "mixed" else 0
         hi = _log(rng, 64, 4000)
         c = _chunk("", model, layers, prompts, plen, past, dec, max(16, hi // rng.randint(1, 8)), hi, vocab,
-                   kind == "chunk" and rng.random() < 0.3, round(rng.uniform(0.1, 0.9), 2) if kind == "routed_chunk" else 0.0)
+                   rng.random() < 0.7, round(rng.uniform(0.1, 0.9), 2) if kind == "routed_chunk" else 0.0)
         c["hi"] = max(c["hi"], c["lo"])
     del c["name"]
     return c
@@ -353,9 +354,7 @@ def run(s):
         for l, (k, v) in enumerate(s.kv_out):
             e.kv_read(l, s.new_slots.data_ptr(), s.new_slots.numel(), k.data_ptr(), v.data_ptr(), s.sp)
         return {"logits": s.logits, "kv": s.kv_out}
-    if s.m.n_layers > 8:  # the pool of a whole model is several GB of mostly unchanged values
-        return {"logits": s.logits}
-    return {"logits": s.logits, "pool": s.pool}
+    return {"logits": s.logits}
 
 
 # ------------------------------------------------------------------ work and tolerance
@@ -483,4 +482,4 @@ def exact(case, seed):
     z = mm(_rms(x[out], f(gain), m.rms_eps), lm_head)
     if case.get("read_kv"):
         return {"logits": z, "kv": kv_out}
-    return {"logits": z} if m.n_layers > 8 else {"logits": z, "pool": None}
+    return {"logits": z}
