@@ -15,16 +15,16 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf2f(uint32_t u16) { return __uint_as_float(u16 << 16); }
 
-// float -> bf16 bits, round to nearest even; NaN stays a (quiet) NaN.
-// Both results are computed and one is selected: no branch per call.
-__device__ __forceinline__ uint32_t f2bf(float f) {
-  const uint32_t u = __float_as_uint(f);
-  const uint32_t rounded = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-  const uint32_t quiet_nan = ((u >> 16) | 0x40u) & 0xffffu;
-  return (u & 0x7fffffffu) > 0x7f800000u ? quiet_nan : rounded;
+// float -> bf16 bits, round to nearest even; NaN stays a (quiet) NaN: one
+// v_cvt_pk_bf16_f32 for two values (all 2^32 floats give the bits of the
+// integer form of the rounding, which took seven operations a value and a
+// third of the attention walk's instructions).
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
-
-__device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) { return f2bf(lo) | (f2bf(hi) << 16); }
+__device__ __forceinline__ uint32_t f2bf(float f) { return pack_bf2(f, 0.f) & 0xffffu; }
 
 // double -> bf16 bits, round to nearest even.  Rounds to float first; that
 // can only mislead the second rounding when the float lands exactly on a bf16

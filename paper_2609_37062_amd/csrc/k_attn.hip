@@ -73,7 +73,8 @@ hipError_t launch_attn_decode(const AttnArgs& a, int n_rows, int grid_splits, in
 // drain every outstanding one before each LDS read.)  A compute wave
 // computes only the pairs holding its tile's first my_cnt blocks.  Keys at
 // t >= t_end do not count (their V is zeroed: stale slots may hold NaN
-// patterns); with MASK a key also needs t <= lim.  Returns true on the waves
+// patterns); with MASK a key also needs t <= lim.  Keys below full_end (the
+// same for the whole wave) count for every column.  Returns true on the waves
 // that hold a tile's result (half 0).
 constexpr int kWalkLead = 2;
 constexpr int kWalkSlots = kWalkLead + 1;
@@ -86,8 +87,8 @@ struct WalkLds {
 template <int D, int NCT, int NH, bool MASK>
 __device__ __forceinline__ bool mq_walk(const u32x4 (&qf)[D / 32], const uint16_t* kbase, const uint16_t* vbase,
                                         size_t kv_stride, const int32_t* tbl, int cnt, int my_cnt, int b0, int lim,
-                                        int t_end, float sc, float& m, float& l, f32x4 (&o)[D / 16],
-                                        WalkLds<D, NH>& sm) {
+                                        int t_end, int full_end, float sc, float& m, float& l,
+                                        f32x4 (&o)[D / 16], WalkLds<D, NH>& sm) {
   constexpr int KC = D / 32;   // K chunks (1 KiB) per block
   constexpr int VC = D / 16;   // V chunks (512 B) per block
   constexpr int NCH = 2 * KC;  // 1 KiB chunks per block
@@ -157,12 +158,18 @@ __device__ __forceinline__ bool mq_walk(const u32x4 (&qf)[D / 32], const uint16_
           const int t0 = kBlock * (b0 + 2 * p);
           PTerms pp;
           float alpha;
-          pair_scores<D, MASK>(qf, kg, t0, t_end, lim, sc, m, l, pp, alpha);
-          pair_pv<D>(vt, t0, t_end, pp, alpha, o);
+          if (t0 + 2 * kBlock <= full_end) {  // (uniform) every key counts for every column
+            pair_scores<D, MASK, true>(qf, kg, t0, t_end, lim, sc, m, l, pp, alpha);
+            pair_pv<D, true>(vt, t0, t_end, pp, alpha, o);
+          } else {
+            pair_scores<D, MASK, false>(qf, kg, t0, t_end, lim, sc, m, l, pp, alpha);
+            pair_pv<D, false>(vt, t0, t_end, pp, alpha, o);
+          }
         }
       }
     }
   }
+  l = walk_sum(l);
   if constexpr (NH > 1) {
     // merge the halves of each tile in a fixed order: halves 1.. hand their
     // (m, l, O) over through the ring's space once every wave is done with it
@@ -245,7 +252,7 @@ __global__ __launch_bounds__(64 * (kPfxWaves + 1)) void k_attn_prefix(AttnPrefix
   const int cnt = b_hi - b_lo;
   const int my_cnt = w < kPfxWaves && col0 + 16 * ct < n_cols ? cnt : 0;
   const bool owner = mq_walk<D, kPfxTiles, kPfxHalves, false>(qf, kbase, vbase, kv_stride, tbl, cnt, my_cnt, b_lo, 0,
-                                                              kBlock * b_hi, a.scale_log2, m, l, o, ring);
+                                                              kBlock * b_hi, kBlock * b_hi, a.scale_log2, m, l, o, ring);
 
   // this item's partial of each valid column, as split `split` of its row;
   // the decode kernel, launched after this one, reads them
@@ -317,8 +324,10 @@ __global__ __launch_bounds__(64 * (kPreTiles + 1)) void k_attn_prefill(AttnPrefi
   // its own last column's block (none if it has no column)
   const int c_last = min(16 * w + 15, n_cols - 1);
   const int w_blocks = w < kPreTiles && 16 * w < n_cols ? a.pos[row0 + c_last / G] / kBlock + 1 : 0;
+  // keys up to the wave's first row's position count for all its columns
+  const int w_full = __builtin_amdgcn_readfirstlane(w_blocks > 0 ? a.pos[row0 + 16 * w / G] + 1 : 0);
   mq_walk<D, kPreTiles, 1, true>(qf, kbase, vbase, kv_stride, tbl, nb, w_blocks, 0, lim, min(kv_end, kBlock * nb),
-                                 a.scale_log2, m, l, o, ring);
+                                 min(kv_end, w_full), a.scale_log2, m, l, o, ring);
   if (!(w < kPreTiles && 16 * w < n_cols)) return;
 
   if (cvalid) {
