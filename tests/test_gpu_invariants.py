@@ -341,6 +341,33 @@ def test_argmax_sample_is_bit_exact(dtype, vocab):
     np.testing.assert_array_equal(ids2.cpu().numpy(), got)
 
 
+@pytest.mark.parametrize("vocab", [40003, 4099, 4096, 15])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_argmax_sample_unaligned_rows(dtype, vocab, offset):
+    """Rows that start and end anywhere in a 16-byte load: the maximum (and a
+    later equal value) in the elements before, inside and after the whole vectors."""
+    from paper_2609_37062_amd import vsk
+    rng = np.random.default_rng(vocab + offset + 7 * dtype)
+    z = np.concatenate([_argmax_rows(vocab, rng)] + [rng.standard_normal((12, vocab))])
+    for i, j in enumerate([0, 1, 7, 8, vocab // 2, vocab - 9, vocab - 8, vocab - 1]):
+        z[9 + i, max(0, min(j, vocab - 1)):vocab:5] = 11.0
+    z[-1] = np.nan
+    z[-1, -1] = -np.inf                                       # the only value of its row
+    t = torch.from_numpy(z.astype(np.float32))
+    t = t.to(torch.bfloat16) if dtype == 0 else t
+    zin = t.float().numpy().astype(np.float64)
+    buf = torch.zeros(t.numel() + offset, dtype=t.dtype, device="cuda")
+    buf[offset:] = t.reshape(-1).cuda()
+    ids = torch.full((len(z),), -7, dtype=torch.int32, device="cuda")
+    vsk.argmax_sample(buf[offset:].data_ptr(), dtype, len(z), vocab, ids.data_ptr(),
+                      torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    want = nm.argmax_lowest(zin)
+    want[-1] = vocab - 1  # (the oracle counts a NaN as -inf; here -inf is a value and NaN is none)
+    np.testing.assert_array_equal(ids.cpu().numpy(), want)
+
+
 def test_argmax_sample_rejects_bad_arguments():
     from paper_2609_37062_amd import vsk
     t = torch.zeros((2, 8), dtype=torch.float32, device="cuda")
