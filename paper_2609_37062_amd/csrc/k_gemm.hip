@@ -31,52 +31,11 @@
 
 #include "dev.hpp"
 #include "gemm.hpp"
+#include "gemm_epi.hpp"
 
 namespace vsk {
 
-__device__ __forceinline__ float silu_f(float v) { return v / (1.0f + expf(-v)); }
-
-// The QKV epilogue of one row and four consecutive packed output columns
-// n0..n0+3 (n0 a multiple of 4): rotary on q and k heads with the factors of
-// packed rows n0, n0 + 2 (cs0, cs1), q to the bf16 buffer, k and v into this
-// layer's KV slot `sl` of the row.
-__device__ __forceinline__ void qkv_store(const GemmArgs& a, int row, int n0, const f32x4 v, int sl, float2 cs0,
-                                          float2 cs1) {
-  const int hd = a.hd, half = hd >> 1;
-  const int blk = sl >> 4, t = sl & 15;
-  if (n0 < a.Nq + a.Nkv) {
-    const int ph = n0 % hd;          // packed row inside the head (multiple of 4)
-    const int hb = n0 - ph;          // first packed row of the head
-    const int j0 = ph >> 1;          // dims j0, j0+half, j0+1, j0+1+half
-    const float y0 = v[0] * cs0.x - v[1] * cs0.y;
-    const float y1 = v[1] * cs0.x + v[0] * cs0.y;
-    const float y2 = v[2] * cs1.x - v[3] * cs1.y;
-    const float y3 = v[3] * cs1.x + v[2] * cs1.y;
-    if (n0 < a.Nq) {
-      uint16_t* q = a.out + static_cast<size_t>(row) * a.Nq + hb;
-      q[j0] = f2bf(y0);
-      q[j0 + half] = f2bf(y1);
-      q[j0 + 1] = f2bf(y2);
-      q[j0 + 1 + half] = f2bf(y3);
-    } else {
-      const int hk = (hb - a.Nq) / hd;
-      uint16_t* kb =
-          a.pool + ((((static_cast<size_t>(a.layer) * 2 + 0) * a.n_blocks + blk) * a.Hkv + hk) * kBlock * hd);
-      kb[kv_k_index(t, j0)] = f2bf(y0);
-      kb[kv_k_index(t, j0 + half)] = f2bf(y1);
-      kb[kv_k_index(t, j0 + 1)] = f2bf(y2);
-      kb[kv_k_index(t, j0 + 1 + half)] = f2bf(y3);
-    }
-  } else {
-    const int nv = n0 - a.Nq - a.Nkv;
-    const int hk = nv / hd, e0 = nv % hd;
-    uint16_t* vb = a.pool + ((((static_cast<size_t>(a.layer) * 2 + 1) * a.n_blocks + blk) * a.Hkv + hk) * kBlock * hd);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) vb[kv_v_index(t, e0 + r)] = f2bf(v[r]);
-  }
-}
-
-template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL>
+template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL, bool NTW>
 __global__ __launch_bounds__(64 * (WN * WK + (XL ? 1 : 0))) void k_gemm(GemmArgs a) {
   static_assert(!XL || (WN * WK == 8 && (WK == 1 || WK == 2 || WK == 4)), "X in LDS: 8 compute waves");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -148,11 +107,13 @@ __global__ __launch_bounds__(64 * (WN * WK + (XL ? 1 : 0))) void k_gemm(GemmArgs
   const u32x4* Wbase = a.W + lane;
   const u32x4* Xbase = a.X + lane;
 
+  // NTW: nothing reads a weight tile again in this launch
+  auto w_tile = [](const u32x4* p) { return NTW ? __builtin_nontemporal_load(p) : *p; };
   u32x4 fa[PF][NT], fb[PF][MG];
   auto load = [&](u32x4 (&ra)[NT], u32x4 (&rb)[MG], int i) {
     const int kt = first + min(i, n_it - 1) * WK;
 #pragma unroll
-    for (int j = 0; j < NT; ++j) ra[j] = Wbase[(static_cast<size_t>(ntc[j]) * a.Kt + kt) * 64];
+    for (int j = 0; j < NT; ++j) ra[j] = w_tile(Wbase + (static_cast<size_t>(ntc[j]) * a.Kt + kt) * 64);
 #pragma unroll
     for (int g = 0; g < MG; ++g) rb[g] = Xbase[(static_cast<size_t>(kt) * a.Rg + gc[g]) * 64];
   };
@@ -297,7 +258,7 @@ __global__ __launch_bounds__(64 * (WN * WK + (XL ? 1 : 0))) void k_gemm(GemmArgs
       auto wload = [&](u32x4 (&r)[NT], int i) {
         const int kt = first + min(i, n_it - 1) * WK;
 #pragma unroll
-        for (int j = 0; j < NT; ++j) r[j] = Wbase[(static_cast<size_t>(ntc[j]) * a.Kt + kt) * 64];
+        for (int j = 0; j < NT; ++j) r[j] = w_tile(Wbase + (static_cast<size_t>(ntc[j]) * a.Kt + kt) * 64);
       };
       if (n_it > 0) {
 #pragma unroll
@@ -514,8 +475,8 @@ __global__ __launch_bounds__(64 * (WN * WK + (XL ? 1 : 0))) void k_gemm(GemmArgs
 }
 
 // ---------------------------------------------------------------- launcher
-template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL = false>
-static hipError_t launch_cfg(const GemmArgs& a_in, int m_tiles, int ksplit, hipStream_t s, const LaunchEvents& ev) {
+template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL, bool NTW>
+static hipError_t launch_ntw(const GemmArgs& a_in, int m_tiles, int ksplit, hipStream_t s, const LaunchEvents& ev) {
   GemmArgs a = a_in;
   a.xcd_remap = a_in.xcd_remap && m_tiles > 1 ? 1 : 0;
   const int n_groups = (a.N / 16 + NT * WN - 1) / (NT * WN);
@@ -526,19 +487,34 @@ static hipError_t launch_cfg(const GemmArgs& a_in, int m_tiles, int ksplit, hipS
     smem = std::max<size_t>(smem, 3 * (MG <= 4 ? 8 : 4) * MG * 64 * sizeof(u32x4));
     // with the static arrays this is more than 64 KiB of LDS: allow it once
     static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k_gemm<MG, NT, WN, WK, PF, EPI, XL>),
+        reinterpret_cast<const void*>(&k_gemm<MG, NT, WN, WK, PF, EPI, XL, NTW>),
         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
     if (attr != hipSuccess) return attr;
   }
   const dim3 block(64 * (WN * WK + (XL ? 1 : 0)));
   if (ev.start != nullptr || ev.stop != nullptr) {
     // events bound to this dispatch: they take its start and end times
-    hipExtLaunchKernelGGL((k_gemm<MG, NT, WN, WK, PF, EPI, XL>), grid, block, static_cast<uint32_t>(smem), s, ev.start,
+    hipExtLaunchKernelGGL((k_gemm<MG, NT, WN, WK, PF, EPI, XL, NTW>), grid, block, static_cast<uint32_t>(smem), s, ev.start,
                           ev.stop, 0u, a);
   } else {
-    hipLaunchKernelGGL((k_gemm<MG, NT, WN, WK, PF, EPI, XL>), grid, block, smem, s, a);
+    hipLaunchKernelGGL((k_gemm<MG, NT, WN, WK, PF, EPI, XL, NTW>), grid, block, smem, s, a);
   }
   return hipGetLastError();
+}
+
+// One row tile reads each weight tile once: non-temporal loads, which keep the
+// stream from displacing what the L2 holds (a pure stream of 235 MB in this
+// order 46.6 -> 43.2 us; the batch-1 pass of four 3B layers and the head 407
+// -> 371 us, batch 128 of four 8B layers 1135 -> 1089).  Row tiles share
+// weight tiles through the L2: ordinary loads.
+template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL = false>
+static hipError_t launch_cfg(const GemmArgs& a, int m_tiles, int ksplit, hipStream_t s, const LaunchEvents& ev) {
+  constexpr bool kOneTile = MG == 1 || MG == 4;    // never row-tiled
+  constexpr bool kRowTiled = MG == 6 || MG == 7 || MG == 11;  // heights of row-tiled passes
+  if constexpr (!kOneTile)
+    if (kRowTiled || m_tiles > 1) return launch_ntw<MG, NT, WN, WK, PF, EPI, XL, false>(a, m_tiles, ksplit, s, ev);
+  if constexpr (!kRowTiled) return launch_ntw<MG, NT, WN, WK, PF, EPI, XL, true>(a, m_tiles, ksplit, s, ev);
+  return hipErrorInvalidValue;
 }
 
 // Launch shapes.  mg = 16-row groups of X per tile.  For mg == 1:
