@@ -65,18 +65,15 @@ __device__ __forceinline__ int attn_row_splits(int kv_len, int bps) {
 // lanes.  The softmax's cross-lane max and sum and the rescale of O run once
 // per 32 keys.
 //
-// K operand of group G: the block (0: A, 1: B) and the 16-byte index within
-// each 1 KiB K chunk (stored in the 16 x 16 x 32 A-operand order of one block:
-// piece key + 16 x dim-group) of the row this lane feeds.
+// K operand of group G: the block (0: A, 1: B) and the 16-byte piece within
+// each 1 KiB K chunk of the row this lane feeds (the block stores its tokens
+// in this order: a group's eight rows of a block are one 128-byte line).
 __device__ __forceinline__ int pair_k_block(int lane) { return (lane & 15) >> 3; }
-__device__ __forceinline__ int pair_k_index(int lane, int grp) {
-  return 8 * ((lane >> 2) & 1) + 4 * grp + (lane & 3) + 16 * (lane >> 4);
-}
+__device__ __forceinline__ int pair_k_index(int lane, int grp) { return (lane & 7) + 8 * grp + 16 * (lane >> 4); }
 // V^T operand: lane (dim i, quarter q) takes keys 8q .. 8q + 7, i.e. block
-// q / 2, as two 8-byte pieces of each 512-byte V chunk (stored in the
-// 16 x 16 x 16 A-operand order of one block): index below, and index + 16.
+// q / 2, one 16-byte piece of each 512-byte V chunk.
 __device__ __forceinline__ int pair_v_block(int lane) { return lane >> 5; }
-__device__ __forceinline__ int pair_v_index(int lane) { return (lane & 15) + 32 * ((lane >> 4) & 1); }
+__device__ __forceinline__ int pair_v_index(int lane) { return lane & 31; }
 
 // The probabilities of a step as the B operand of P V, split into kPTerms
 // bf16 terms whose sum is the float32 probability to about 8 kPTerms
@@ -259,7 +256,12 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int row, int hk, in
                           static_cast<size_t>(hk) * kBlock * D;
 
   // K and V operands of blocks 2p, 2p + 1 of this wave's range (a block past
-  // the range: its last block again, whose keys the step then masks)
+  // the range: its last block again, whose keys the step then masks).  Every
+  // load takes whole 128-byte lines (the pool's order of tokens), and a pass
+  // reads them once: non-temporal.  With half lines per load (8-byte V
+  // pieces) non-temporal loads fetched lines twice: 8B at 37 rows of
+  // 100-6,000 tokens 989 us ordinary, 1,013 non-temporal, 935 with whole
+  // lines; 128 rows 1,089, 1,049, 1,029.
   auto pair_blocks = [&](int p, int cnt, int w_lo, size_t& bA, size_t& bB) {
     bA = static_cast<size_t>(sm.tbl[w_lo + min(2 * p, cnt - 1)]);
     bB = static_cast<size_t>(sm.tbl[w_lo + min(2 * p + 1, cnt - 1)]);
@@ -271,20 +273,17 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int row, int hk, in
     const int k0 = pair_k_index(lane, 0), k1 = pair_k_index(lane, 1);
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      kg[0][c] = kp[c * 64 + k0];
-      kg[1][c] = kp[c * 64 + k1];
+      kg[0][c] = __builtin_nontemporal_load(kp + c * 64 + k0);
+      kg[1][c] = __builtin_nontemporal_load(kp + c * 64 + k1);
     }
   };
   auto load_v = [&](u32x4 (&vt)[VC], int p, int cnt, int w_lo) {
     size_t bA, bB;
     pair_blocks(p, cnt, w_lo, bA, bB);
-    const u32x2* vp =
-        reinterpret_cast<const u32x2*>(vbase + (pair_v_block(lane) ? bB : bA) * kv_stride) + pair_v_index(lane);
+    const u32x4* vp =
+        reinterpret_cast<const u32x4*>(vbase + (pair_v_block(lane) ? bB : bA) * kv_stride) + pair_v_index(lane);
 #pragma unroll
-    for (int c = 0; c < VC; ++c) {
-      const u32x2 lo = vp[c * 64], hi = vp[c * 64 + 16];
-      vt[c] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-    }
+    for (int c = 0; c < VC; ++c) vt[c] = __builtin_nontemporal_load(vp + c * 32);
   };
 
   __syncthreads();  // sm.tbl

@@ -8,7 +8,6 @@
 namespace vsk {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -45,12 +44,6 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-// D(16x16,f32) += A(16x16) * B(16x16), bf16 operands, 4 per lane.
-__device__ __forceinline__ f32x4 mfma_16x16x16(u32x2 a, u32x2 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4_t, a),
-                                                   __builtin_bit_cast(bf16x4_t, b), c, 0, 0, 0);
-}
-
 // Write-through stores (sc1): the data goes to memory instead of staying in
 // this XCD's L2, so a workgroup on another XCD of the same launch reads it
 // once this wave's memory counter has drained.  Plain stores are only made

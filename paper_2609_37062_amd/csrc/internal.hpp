@@ -56,17 +56,22 @@ __host__ __device__ inline size_t frag_index(int row, int k, int Rg) {
 
 // ---------------------------------------------------------------- KV pool
 // Pool = [L][2][n_blocks][n_kv_heads][block of 16 tokens x head_dim] bf16.
-// K block: chunk c = dim/32 (1 KiB each): lane t + 16*((dim%32)/8), elem dim%8
-//          (A-operand order of the 16x16x32 MFMA for S = K q).
-// V block: chunk c = dim/16 (512 B each): lane dim%16 + 16*(t/4), elem t%4
-//          (A-operand order of the 16x16x16 MFMA for O^T = V^T P^T).
+// K block: chunk c = dim/32 (1 KiB each): 16-byte piece p + 16*((dim%32)/8),
+//          elem dim%8, where p is token t with bits 2 and 3 swapped: attention
+//          takes tokens {0-3, 8-11} with one load and {4-7, 12-15} with the
+//          next, and each is then whole 128-byte lines (S = K q on the
+//          16x16x32 MFMA).
+// V block: chunk c = dim/16 (512 B each): 16-byte piece dim%16 + 16*(t/8),
+//          elem t%8 (eight tokens of a dim: what a lane feeds to O^T = V^T P^T
+//          on the 16x16x32 MFMA, in one load).
 __host__ __device__ inline int kv_k_index(int t, int e) {
   const int c = e >> 5, ee = e & 31;
-  return ((c * 64) + t + 16 * (ee >> 3)) * 8 + (ee & 7);
+  const int p = (t & 3) | ((t & 4) << 1) | ((t & 8) >> 1);
+  return ((c * 64) + p + 16 * (ee >> 3)) * 8 + (ee & 7);
 }
 __host__ __device__ inline int kv_v_index(int t, int e) {
   const int c = e >> 4;
-  return ((c * 64) + (e & 15) + 16 * (t >> 2)) * 4 + (t & 3);
+  return ((c * 32) + (e & 15) + 16 * (t >> 3)) * 8 + (t & 7);
 }
 
 // ---------------------------------------------------------------- device batch

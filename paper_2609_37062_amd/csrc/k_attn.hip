@@ -108,11 +108,11 @@ __device__ __forceinline__ bool mq_walk(const u32x4 (&qf)[D / 32], const uint16_
 #pragma unroll
           for (int hb = 0; hb < 2; ++hb) {
             const size_t blk = static_cast<size_t>(tbl[min(2 * (st * NH + hp) + hb, cnt - 1)]);
-            // block B's K pieces land swizzled (piece j at slot j ^ 4): a
+            // block B's K pieces land swizzled (piece j at slot j ^ 8): a
             // compute wave's 16 lanes of one LDS read phase then take 16
             // distinct 16-byte bank groups (8 from each block) instead of
             // the same 8 twice
-            const u32x4* kp = reinterpret_cast<const u32x4*>(kbase + blk * kv_stride) + (lane ^ (hb ? 4 : 0));
+            const u32x4* kp = reinterpret_cast<const u32x4*>(kbase + blk * kv_stride) + (lane ^ (hb ? 8 : 0));
             const u32x4* vp = reinterpret_cast<const u32x4*>(vbase + blk * kv_stride) + lane;
 #pragma unroll
             for (int g = 0; g < NCH; ++g)
@@ -135,14 +135,14 @@ __device__ __forceinline__ bool mq_walk(const u32x4 (&qf)[D / 32], const uint16_
     } else {
       const int my_pairs = (my_cnt + 1) / 2;
       const int kb = pair_k_block(lane), k0 = pair_k_index(lane, 0), k1 = pair_k_index(lane, 1);
-      const int ksw = kb ? 4 : 0;  // block B's K pieces are stored swizzled (see the loader)
+      const int ksw = kb ? 8 : 0;  // block B's K pieces are stored swizzled (see the loader)
       const int vb = pair_v_block(lane), vi = pair_v_index(lane);
       for (int st = 0; st < n_steps; ++st) {
         barrier_after_lds_reads();
         const int p = st * NH + hh;
         if (p < my_pairs) {
           const u32x4* kp = &sm.ring[st % kWalkSlots][hh][kb][0][0];
-          const u32x2* vp = reinterpret_cast<const u32x2*>(&sm.ring[st % kWalkSlots][hh][vb][KC][0]) + vi;
+          const u32x4* vp = &sm.ring[st % kWalkSlots][hh][vb][KC][0] + vi;
           u32x4 kg[2][KC];
           u32x4 vt[VC];
 #pragma unroll
@@ -151,10 +151,7 @@ __device__ __forceinline__ bool mq_walk(const u32x4 (&qf)[D / 32], const uint16_
             kg[1][c] = kp[c * 64 + (k1 ^ ksw)];
           }
 #pragma unroll
-          for (int c = 0; c < VC; ++c) {
-            const u32x2 lo = vp[c * 64], hi = vp[c * 64 + 16];
-            vt[c] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-          }
+          for (int c = 0; c < VC; ++c) vt[c] = vp[c * 32];
           const int t0 = kBlock * (b0 + 2 * p);
           PTerms pp;
           float alpha;
