@@ -41,16 +41,16 @@ PackedLayout packed_layout(const vsk_model_cfg& c) {
   size_t o = 0;
   p.l.attn_norm = o; o = align_up(o + H * 2);
   p.l.mlp_norm = o; o = align_up(o + H * 2);
-  p.l.wqkv = o; o = align_up(o + (Nq + 2 * Nkv) * H * 2);
-  p.l.wo = o; o = align_up(o + H * Nq * 2);
-  p.l.wgu = o; o = align_up(o + 2 * F * H * 2);
-  p.l.wd = o; o = align_up(o + H * F * 2);
+  p.l.wqkv = o; o = align_up(o + w_bytes(Nq + 2 * Nkv, H));
+  p.l.wo = o; o = align_up(o + w_bytes(H, Nq));
+  p.l.wgu = o; o = align_up(o + w_bytes(2 * F, H));
+  p.l.wd = o; o = align_up(o + w_bytes(H, F));
   p.layer_bytes = o;
   p.head_base = p.layer_bytes * c.n_layers;
   o = p.head_base;
   p.final_norm = o; o = align_up(o + H * 2);
   p.embed = o; o = align_up(o + V * H * 2);
-  p.lm_head = o; o = align_up(o + V * H * 2);
+  p.lm_head = o; o = align_up(o + w_bytes(V, H));
   p.rope = o; o = align_up(o + static_cast<size_t>(c.max_pos) * (c.head_dim / 2) * 8);
   p.total = o;
   return p;
@@ -621,9 +621,9 @@ static size_t routed_layer_bytes(const vsk_model_cfg& c, int32_t proj_ffn, size_
   const size_t H = c.hidden, Fp = proj_ffn;
   size_t o = 0;
   if (pgu) *pgu = o;
-  o = align_up(o + 2 * Fp * H * 2);
+  o = align_up(o + w_bytes(2 * Fp, H));
   if (pd) *pd = o;
-  o = align_up(o + H * Fp * 2);
+  o = align_up(o + w_bytes(H, Fp));
   return o;
 }
 

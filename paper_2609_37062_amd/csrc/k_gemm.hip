@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * (WN * WK + (XL ? 1 : 0))) void k_gemm(GemmArgs
   auto load = [&](u32x4 (&ra)[NT], u32x4 (&rb)[MG], int i) {
     const int kt = first + min(i, n_it - 1) * WK;
 #pragma unroll
-    for (int j = 0; j < NT; ++j) ra[j] = w_tile(Wbase + (static_cast<size_t>(ntc[j]) * a.Kt + kt) * 64);
+    for (int j = 0; j < NT; ++j) ra[j] = w_tile(Wbase + (static_cast<size_t>(ntc[j]) * w_stride(a.Kt) + kt) * 64);
 #pragma unroll
     for (int g = 0; g < MG; ++g) rb[g] = Xbase[(static_cast<size_t>(kt) * a.Rg + gc[g]) * 64];
   };
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(64 * (WN * WK + (XL ? 1 : 0))) void k_gemm(GemmArgs
       auto wload = [&](u32x4 (&r)[NT], int i) {
         const int kt = first + min(i, n_it - 1) * WK;
 #pragma unroll
-        for (int j = 0; j < NT; ++j) r[j] = w_tile(Wbase + (static_cast<size_t>(ntc[j]) * a.Kt + kt) * 64);
+        for (int j = 0; j < NT; ++j) r[j] = w_tile(Wbase + (static_cast<size_t>(ntc[j]) * w_stride(a.Kt) + kt) * 64);
       };
       if (n_it > 0) {
 #pragma unroll

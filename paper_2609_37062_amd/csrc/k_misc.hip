@@ -573,7 +573,8 @@ __global__ __launch_bounds__(256) void k_pack(const uint16_t* __restrict__ s0, c
     src = s2;
     lr -= n0 + n1;
   }
-  *reinterpret_cast<u32x4*>(dst + chunk * 8) = *reinterpret_cast<const u32x4*>(src + static_cast<size_t>(lr) * K + k0);
+  const size_t to = (static_cast<size_t>(nt) * w_stride(Kt) + kt) * 64 + lane;
+  *reinterpret_cast<u32x4*>(dst + to * 8) = *reinterpret_cast<const u32x4*>(src + static_cast<size_t>(lr) * K + k0);
 }
 
 hipError_t launch_pack(const uint16_t* s0, const uint16_t* s1, const uint16_t* s2, int n0, int n1, int N, int K,

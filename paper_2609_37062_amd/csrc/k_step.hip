@@ -383,7 +383,7 @@ __device__ __forceinline__ bool gemm_phase(const GemmPh& g, const Epi& e, const 
     const bool past_ = lu >= g.u_hi;                                          \
     const int u_ = past_ ? g.u_hi - 1 : lu;                                   \
     const int i_ = past_ ? S - 1 : li;                                        \
-    wr[s] = Wg[(static_cast<size_t>(u_) * g.Kt + kWaves * i_) * 64];          \
+    wr[s] = Wg[(static_cast<size_t>(u_) * w_stride(g.Kt) + kWaves * i_) * 64];          \
     if (WITH_X) {                                                             \
       xr[s] = Xg[static_cast<size_t>(kWaves * xi) * 64];                      \
       if (++xi == S) xi = 0;                                                  \
