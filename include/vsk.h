@@ -382,15 +382,15 @@ int vsk_set_probe(vsk_handle* h, int32_t which, void* const* begin_events,
  *        2048, with hidden at most 4096, and returns VSK_E_UNSUPPORTED for
  *        other passes.  Both paths compute the same values.
  * key 3: launch shape of the per-operation projections for 17..128 rows
- *        (and longer row-tiled passes).  0 (default): with one row tile the
- *        activation chunks are staged in LDS by a ninth wave and shared by
- *        eight weight-streaming waves for QKV (K split over workgroups in
- *        the residual projections' staging, key 7; unsplit, two 16-column
- *        tiles per workgroup), gate/up (four; eight, two per wave, for 65
- *        rows or more) and lm_head (sixteen, two per wave, no K split in
- *        the workgroup), residual projections taking the four-tile (17..64
- *        rows) or eight-tile (65..128 rows) staging with K split over
- *        workgroups (key 5); passes of more than 128 rows
+ *        (and longer row-tiled passes).  0 (the default): 17..64 rows take
+ *        the kernel that copies both operands into LDS (64, 128 or 256
+ *        columns per workgroup, whichever moves the fewest bytes through a
+ *        compute unit; residual projections and QKV with K split over
+ *        workgroups, keys 5 and 7).  65..128 rows: the activation chunks are
+ *        staged in LDS by a ninth wave and shared by eight weight-streaming
+ *        waves, for gate/up and lm_head over eight and sixteen 16-column
+ *        tiles (two per wave), residual projections and QKV over eight with
+ *        K split over workgroups (QKV unsplit: two).  More than 128 rows
  *        take the staging with the eight waves side by side (16 tiles, 8
  *        for QKV).  1 one column of K-split waves, one tile, every
  *        projection; 2 the same with two tiles; 3 the 2 x 2 grid everywhere;
@@ -404,8 +404,7 @@ int vsk_set_probe(vsk_handle* h, int32_t which, void* const* begin_events,
  *        them once per sequence.
  * key 5: residual projections (O, down) of passes of at most 128 rows: the
  *        workgroup count their K split aims for (1..4096); 0 (the default):
- *        192 workgroups in the activation-staged layout at 17..64 rows, 384
- *        at 65..128, 192 for the down projection at 1..16 rows (two tiles
+ *        at most 256 workgroups at 17..64 rows, 384 at 65..128, 192 for the down projection at 1..16 rows (two tiles
  *        per workgroup), no split for O at 1..16 rows (measured no faster);
  *        -1: no split.  Split products are added to the residual in
  *        split order by the RMSNorm that follows.  Passes of more than 128
@@ -417,9 +416,8 @@ int vsk_set_probe(vsk_handle* h, int32_t which, void* const* begin_events,
  *        head) pairs reading each key block once for all of them; 0 one
  *        work item per row, as for decode rows.
  * key 7: the QKV projection of passes of 17..128 rows: the workgroup count
- *        its K split aims for (1..4096); 0 (the default): 192; -1: no split
- *        (two 16-column tiles per workgroup with the epilogue in the
- *        projection).  Split products are added in split order by a kernel
+ *        its K split aims for (1..4096); 0 (the default): 256 at 17..64 rows,
+ *        192 above; -1: no split (the epilogue in the projection).  Split products are added in split order by a kernel
  *        that then applies rotary and writes q and the KV slots.  Passes of
  *        more than 128 rows split QKV the same way when the residual
  *        layout would give it at most 128 workgroups (within 256 after the

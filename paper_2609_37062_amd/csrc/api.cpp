@@ -1105,7 +1105,8 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   // bytes), the products added by k_qkv_reduce, which applies the epilogue
   GemmPlan p_qkv_split;
   if (h.qkv_target >= 0 && p_qkv.mg >= 4)
-    p_qkv_split = plan_gemm(Nq + 2 * Nkv, H, R, EPI_RESID, h.gemm_shape, h.qkv_target > 0 ? h.qkv_target : kQkvTargetWgs);
+    p_qkv_split = plan_gemm(Nq + 2 * Nkv, H, R, EPI_RESID, h.gemm_shape,
+                            h.qkv_target > 0 ? h.qkv_target : p_qkv.tiled ? kTiledTargetWgs : kQkvTargetWgs);
   const GemmPlan p_o = plan_gemm(H, Nq, R, EPI_RESID, h.gemm_shape, rt, h.row_tile);
   const GemmPlan p_gu = plan_gemm(2 * F, H, R, EPI_SWIGLU, h.gemm_shape, 0, h.row_tile);
   const GemmPlan p_d = plan_gemm(H, F, R, EPI_RESID, h.gemm_shape, rt, h.row_tile);

@@ -37,11 +37,14 @@ struct GemmPlan {
   int nt = 1;        // N tiles per wave
   int wn = 1;        // waves side by side along N
   int ksplit = 1;    // RESID: workgroups along K, their products added by k_resid_norm
+  bool tiled = false;  // k_gemm_tiled (17..64 rows): n_groups of nt x wn column tiles
   bool xl = false;   // X chunks staged in LDS by a loader wave, shared by the compute waves
 };
 
 constexpr int kMaxResidSplits = 8;
 constexpr int kResidTargetWgs = 0;  // default split-K target of the residual projections (0: no split)
+constexpr int kTiledGroups = 4;       // 16-row groups of a k_gemm_tiled launch
+constexpr int kTiledTargetWgs = 256;  // default split-K target at 17..64 rows: one round of compute units
 constexpr int kQkvTargetWgs = 192;  // default split-K target of QKV at 4..8 row groups
 constexpr int kRowTiledSplitBelow = 128;  // row-tiled residual projections split K at or below these workgroups
 constexpr int kRowTiledTarget = 256;      // into as many splits as stay within this many workgroups
@@ -55,6 +58,15 @@ constexpr int kComputeUnits = 256;        // MI355X: 8 XCDs x 32 compute units
 // row_tile: 16-row groups per tile of a row-tiled projection other than the
 // lm_head (0: chosen from the launch rounds; 6, 7, 8 or 11: that height)
 GemmPlan plan_gemm(int N, int K, int R, int epi, int shape = 0, int resid_target = 0, int row_tile = 0);
+// The plan of a projection of 17..64 rows in k_gemm_tiled.  target: for EPI_RESID
+// the workgroups a K split may reach (0: no split).  Of 64, 128 and 256 columns
+// per workgroup it takes the one whose compute units move the fewest bytes
+// (rounds x K steps x (row groups + column tiles)), which ranks the layouts as
+// measured: 28672 x 4096 at 64 rows 64 / 128 / 256 columns 46.5 / 39.5 / 58.0
+// us, 16384 x 3072 18.9 / 25.5 / 40.1, 32000 x 4096 at 37 rows 46.4 / 42.7 /
+// 59.6, 128256 x 3072 at 64 rows 159 / 148 / 139.
+GemmPlan plan_tiled(int N, int K, int R, int epi, int target);
+hipError_t launch_gemm_tiled(const GemmArgs& a, const GemmPlan& p, int epi, hipStream_t s, const LaunchEvents& ev);
 hipError_t launch_gemm(GemmArgs a, const GemmPlan& p, int epi, hipStream_t s, LaunchEvents ev = {});
 // QKV with K split: add the `splits` products in a.ypart and apply the QKV
 // epilogue (a as for the QKV projection, with N = Nq + 2 Nkv).

@@ -1,4 +1,4 @@
-// Epilogue pieces of the projection kernels (k_gemm.hip).
+// Epilogue pieces of the projection kernels (k_gemm.hip, k_gemm_tiled.hip).
 #pragma once
 
 #include "dev.hpp"

@@ -35,7 +35,8 @@ inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a
 // side, and rows a multiple of 64 KiB apart keep meeting in the same memory
 // channels: a pure stream of 28672 x 4096 43.3 us without the four, 37.5 with
 // them, of 128256 x 4096 168 and 153 (two more 38.1 / 157, eight 37.7 / 153);
-// at K = 3072 (96 KiB rows) they change nothing.
+// gate/up of that size at 16 rows 49.1 and 41.3, at 37 rows 41.5 and 40.8, at
+// 128 the same.  At K = 3072 (96 KiB rows) they change nothing.
 __host__ __device__ inline int w_stride(int Kt) { return Kt % 64 == 0 ? Kt + 4 : Kt; }
 inline size_t w_bytes(size_t N, size_t K) { return N / 16 * w_stride(static_cast<int>(K / 32)) * 1024; }
 

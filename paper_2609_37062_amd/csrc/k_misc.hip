@@ -221,7 +221,9 @@ hipError_t launch_resid_norm(float* x, const float* y, int splits, int R, int H,
   const int threads = (H / 8 + 63) / 64 * 64;
   switch (splits) {
     case 2: hipLaunchKernelGGL(k_resid_norm<2>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    case 3: hipLaunchKernelGGL(k_resid_norm<3>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
     case 4: hipLaunchKernelGGL(k_resid_norm<4>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    case 5: hipLaunchKernelGGL(k_resid_norm<5>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
     case 8: hipLaunchKernelGGL(k_resid_norm<8>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
     default: hipLaunchKernelGGL(k_resid_norm<0>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc);
   }

@@ -125,6 +125,45 @@ def test_integer_inputs_bit_exact_row_tiled(variant, rows):
     d.release()
 
 
+# 17..64 rows: gate/up in 128-column workgroups, the head in 256-column ones
+# (the last one ragged), K of 34 and 258 steps split unevenly over workgroups
+WIDE = ModelCfg("wide-2L", n_layers=2, hidden=1088, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=8256,
+                vocab=33088, rope_theta=500000.0)
+
+
+@pytest.mark.parametrize("split", [True, False])
+@pytest.mark.parametrize("rows", [17, 33, 64])
+@pytest.mark.parametrize("variant", ["qkv", "o", "mlp"])
+def test_integer_inputs_bit_exact_17_to_64_rows(variant, rows, split):
+    """Every epilogue of the projections of 17..64 rows, with K split over
+    workgroups (the default) and without (keys 5 and 7 at -1), bit for bit
+    against the oracle."""
+    m = WIDE
+    w = fresh_workload(m, rows, seed=rows, name=f"int-wide-{variant}-r{rows}-{split}")
+    over = int_overrides(m, variant, seed=rows)
+    d = _device(w, overrides=over)
+    if not split:
+        d.eng.set_tuning(5, -1)
+        d.eng.set_tuning(7, -1)
+    d.step()
+    lg, ids = d.results()
+    x_dev = d.residual()
+    a, batch, sub, r, kv, idx = oracle_state(w)
+    out = forward(m, GeneratedWeights(m, w.seed, overrides=over), kv, sub, w.tokens[r], np.arange(rows),
+                  want_hidden=True)
+    for l in range(m.n_layers if variant == "qkv" else 1):
+        K, V = d.read_kv(l, sub["slot"])
+        Ko, Vo = kv.read(l, sub["slot"])
+        np.testing.assert_array_equal(K, Ko)
+        np.testing.assert_array_equal(V, Vo)
+    if variant == "qkv":
+        np.testing.assert_array_equal(lg, out["logits"])
+        np.testing.assert_array_equal(ids, out["ids"])
+    else:
+        np.testing.assert_array_equal(x_dev, out["x"])
+    d.release()
+
+
 # ---------------------------------------------------------------- attention invariants
 def _probe_overrides(m, v_row):
     """Embedding rows of ones (the normed input is exactly 1), Wv making every
