@@ -1026,12 +1026,14 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   const bool cascade = h.shared_prefix != 0 && b.n_pfx_items > 0 && pa.logit_rows == nullptr;
   // the blocks each row of the decode kernel walks (after its shared prefix)
   int blk_min = INT_MAX, blk_max = 0, n_dec = 0;
+  int64_t blk_sum = 0;
   {
     const BatchHost& bh = h.bh;
     auto row_blocks = [&](int r) {
       const int nb = (bh.pos[r] + 1 + kBlock - 1) / kBlock - (cascade ? bh.pfx_blocks[r] : 0);
       blk_min = std::min(blk_min, nb);
       blk_max = std::max(blk_max, nb);
+      blk_sum += nb;
       ++n_dec;
     };
     if (h.prefill_attn != 0 && b.n_pre_items > 0 && b.max_kv_len <= kMaxPrefillBlocks * kBlock) {
@@ -1044,9 +1046,13 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   // 128..255 (row, KV head) pairs whose walks are within 20% of each other:
   // one split per pair (no merge, and the items are balanced already); a
   // wider spread keeps the split, the longest walk setting the time, and
-  // fewer pairs keep it for the parallelism
+  // fewer pairs keep it for the parallelism.  Nor is any walk cut that is no
+  // longer than what each of the kAttnSlots workgroups in flight has to walk
+  // in all (8B, 100 rows of 1,500 to 2,500 tokens: 1,202 us for four layers at
+  // 96 blocks a split, 1,114 uncut).
   const int pairs = n_dec * c.n_kv_heads;
-  if (h.attn_bps == 0 && pairs >= 128 && pairs < 256 && 5 * blk_min >= 4 * blk_max)
+  if (h.attn_bps == 0 && ((pairs >= 128 && pairs < 256 && 5 * blk_min >= 4 * blk_max) ||
+                          blk_sum * c.n_kv_heads >= static_cast<int64_t>(kAttnSlots) * blk_max))
     aa.bps = std::clamp((blk_max + 7) / 8 * 8, kAttnMinBps, kAttnMaxBps);
   aa.max_splits = attn_splits(b.max_kv_len, aa.bps);
   aa.part_o = reinterpret_cast<float*>(ws + wl.att_o);

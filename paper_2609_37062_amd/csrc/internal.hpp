@@ -147,6 +147,8 @@ inline int attn_splits(int kv_len, int bps) {
 // 96 and 128 blocks best, 64 and 160 or more slower).
 inline int attn_auto_bps(int n_rows, int n_kv_heads) { return n_rows * n_kv_heads >= 256 ? 96 : 32; }
 
+constexpr int kAttnSlots = 512;  // decode work items in flight: two per compute unit
+
 struct Handle {
   vsk_model_cfg cfg{};
   std::string err;

@@ -162,6 +162,23 @@ def test_mid_qkv_k_splits(cfg, B, target):
     print(st)
 
 
+def test_mid_uncut_walks_past_96_blocks():
+    """290 rows x 2 KV heads (580 pairs): no walk is longer than a 512th of all
+    of them, so contexts of 98..107 blocks, past the 96-block split, are one
+    work item each; against the oracle."""
+    from paper_2609_37062_amd.runner import DeviceRun
+    B = 290
+    ctx = np.random.default_rng(77).integers(1560, 1700, size=B)
+    w = decode_workload(MID, ctx, seed=31, name="mid-uncut")
+    print(f"[gpu] {w.name}", flush=True)
+    d = DeviceRun(w, poison_pool=True)
+    d.step()
+    assert d.eng.exec_counters()[3] == 1  # one split per row
+    lg, ids = d.results()
+    st, *_ = _check(w, lg, ids, [0, 17, 144, 289])
+    print(st)
+
+
 @pytest.mark.parametrize("lo,hi", [(900, 1000), (300, 1000)])
 def test_mid_auto_split_balance(lo, hi):
     """The automatic attention split at 80 rows x 2 KV heads (160 pairs, fewer
