@@ -72,7 +72,9 @@ WsLayout ws_layout(const vsk_model_cfg& c, int32_t max_rows, int32_t max_seqs, i
   const int G = c.n_q_heads / c.n_kv_heads;
   size_t o = 0;
   w.x = o; o = align_up(o + static_cast<size_t>(max_rows) * H * 4);
-  w.x_c = o; o = align_up(o + static_cast<size_t>(max_rows) * H * 4);
+  // (two unused regions, here and after ssq: a workspace keeps its size, and
+  // vsk_decode_step_scratch the batches it takes)
+  o = align_up(o + static_cast<size_t>(max_rows) * H * 4);
   w.fa = o; o = align_up(o + Rp * Nq * 2);
   w.fb = o; o = align_up(o + Rp * H * 2);
   w.fc = o; o = align_up(o + Rp * F * 2);
@@ -83,7 +85,7 @@ WsLayout ws_layout(const vsk_model_cfg& c, int32_t max_rows, int32_t max_seqs, i
   w.att_cnt = o; o = align_up(o + rh * 4);  // zeroed at init, left zero by every pass
   // x^2 partials: at most one per 16 columns of the hidden size, per row
   w.ssq = o; o = align_up(o + (H / 16) * static_cast<size_t>(max_rows) * 8);
-  w.ssq_c = o; o = align_up(o + (H / 16) * static_cast<size_t>(max_rows) * 8);
+  o = align_up(o + (H / 16) * static_cast<size_t>(max_rows) * 8);
   // residual projections with K split over workgroups: one product per split
   // and row (and the QKV projection's, N = Nq + 2 Nkv); row-tiled passes with
   // few workgroups split too
@@ -596,11 +598,10 @@ int vsk_decode_step_scratch(vsk_handle* h, const int32_t* ids_dev, void* logits_
   hipError_t e = scratch_base(&base);
   if (e != hipSuccess) return hip_check(h, e, "scratch address");
   hipStream_t s = static_cast<hipStream_t>(stream);
+  PassArgs a{ids_dev, nullptr, b.n_rows, static_cast<uint16_t*>(logits_dev), next_ids_dev, base, wl};
   // the attention arrival counters must start at zero; the layout (and so
   // their place) follows the batch, and the array keeps the last call's bytes
-  e = launch_fill_zero(base + wl.att_cnt, static_cast<size_t>(b.n_rows) * h->cfg.n_kv_heads * 4, s);
-  if (e != hipSuccess) return hip_check(h, e, "scratch counters");
-  PassArgs a{ids_dev, nullptr, b.n_rows, static_cast<uint16_t*>(logits_dev), next_ids_dev, base, wl};
+  a.clear_counters = true;
   return hip_check(h, run_pass(*h, a, s), "decode step (scratch)");
 }
 
@@ -990,7 +991,10 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
     return launch(ev);
   };
 
-  TRY(launch_embed(reinterpret_cast<const uint16_t*>(P + h.pl.embed), pa.ids, R, H, c.vocab, x, ssq, s));
+  TRY(launch_embed_norm(reinterpret_cast<const uint16_t*>(P + h.pl.embed), pa.ids, R, H, c.vocab, x,
+                        norm_gain(0, false), c.rms_eps, fb, Rg,
+                        pa.clear_counters ? reinterpret_cast<int*>(ws + wl.att_cnt) : nullptr,
+                        pa.clear_counters ? R * c.n_kv_heads : 0, s));
   int ssq_parts = 1;
 
   GemmArgs ga{};
@@ -1147,7 +1151,7 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   // a residual projection: in place (x += y, with x^2 partials), or with K
   // split over workgroups and the splits added by k_resid_norm, which also
   // normalises the rows with `next_gain` (null: no norm follows here)
-  bool normed = false;  // fb already holds the normalised input of the next projection
+  bool normed = true;  // fb already holds the normalised input of the next projection
   auto resid = [&](int cls, const GemmPlan& p, const uint16_t* next_gain) -> hipError_t {
     hipError_t re;
     if (p.ksplit > 1) {
@@ -1287,10 +1291,7 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   const int Ro = pa.n_logit_rows;
   const int Rgo = (Ro + 15) / 16;
   if (pa.logit_rows != nullptr) {
-    float* x_c = reinterpret_cast<float*>(ws + wl.x_c);
-    double* ssq_c = reinterpret_cast<double*>(ws + wl.ssq_c);
-    TRY(launch_gather_rows(x, R, pa.logit_rows, Ro, H, x_c, ssq_c, s));
-    TRY(norm(final_gain, x_c, Ro, Rgo, ssq_c, 1));
+    TRY(launch_gather_norm(x, R, pa.logit_rows, Ro, H, final_gain, c.rms_eps, fb, Rgo, s));
   } else if (!normed) {
     TRY(norm(final_gain, x, Ro, Rgo, ssq, ssq_parts));
   }

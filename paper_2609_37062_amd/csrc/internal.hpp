@@ -117,7 +117,7 @@ struct LaunchEvents {
 
 struct WsLayout {
   int32_t max_rows = 0, max_seqs = 0, max_kv_len = 0, Rg = 0, max_splits = 0;
-  size_t x, x_c, fa, fb, fc, q, att_o, att_ml, att_cnt, ssq, ssq_c, am_part, total;
+  size_t x, fa, fb, fc, q, att_o, att_ml, att_cnt, ssq, am_part, total;
   size_t ypart = 0;  // products of residual projections with K split over workgroups
   // routed layers (present when `routed`): Project-Only cohort frags of the
   // MLP input and of the SwiGLU product, both cohorts' down-projection
@@ -243,6 +243,8 @@ struct PassArgs {
   // (1 RUN, 0 Project-Only) and weights w [L_r][rows]
   const uint8_t* tape_run = nullptr;
   const float* tape_w = nullptr;
+  // the attention arrival counters hold no zeros yet: the pass clears them first
+  bool clear_counters = false;
 };
 hipError_t run_pass(Handle& h, const PassArgs& a, hipStream_t s);
 // True when run_pass would take the persistent step kernel for this pass.

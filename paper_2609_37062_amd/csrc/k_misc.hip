@@ -1,4 +1,4 @@
-// Small kernels of the pass: embedding gather, logit-row gather, greedy
+// Small kernels of the pass: embedding and logit rows with their norms, greedy
 // argmax, weight repacking, KV scatter/gather, workspace clearing.
 #include <climits>
 #include <cmath>
@@ -9,75 +9,86 @@
 
 namespace vsk {
 
-// ---------------------------------------------------------------- embedding
-// x[r][:] = float(E[ids[r]][:]) (fp32 residual), plus what the first QKV
-// projection consumes: frags of bf16(x * g) and per-16-column partial sums
-// of x^2 (one per row: ssq[r]).  Token ids outside [0, V) give a zero row.
-__global__ __launch_bounds__(256) void k_embed(const uint16_t* __restrict__ E, const int32_t* __restrict__ ids,
-                                               int H, int V, float* __restrict__ x, double* __restrict__ ssq) {
-  __shared__ double s_ss[4];
+// ---------------------------------------------------------------- first and last norm
+// The rows a norm of a pass starts from, and that norm, one workgroup per row
+// and one thread per 8 columns: x[r] = float(E[ids[r]]) and the first layer's
+// attention norm (EMBED), or row rows[r] of the residual stream and the final
+// norm (a prefill pass returns logits for a few rows out of many).  Indices
+// outside the table give a zero row.  The sum of squares in double, added in a
+// fixed order, the product in double and rounded once, as in k_resid_norm.
+// What bounds it is the launch: gather and norm as two kernels took 4-5 us
+// each at a few rows (12.5 and 16 for 2,080), as one 4.6-5
+// (21).
+// EMBED also clears the `n_zero` words at `zero` (a caller's arrival counters).
+template <bool EMBED>
+__global__ __launch_bounds__(1024) void k_first_norm(const void* __restrict__ src, const int32_t* __restrict__ idx,
+                                                     int n_src, int H, float* __restrict__ x,
+                                                     const uint16_t* __restrict__ g, float eps,
+                                                     uint16_t* __restrict__ hg, int Rg, int* __restrict__ zero,
+                                                     int n_zero) {
+  __shared__ double s_ss[16];
   const int r = blockIdx.x;
-  const int id = ids[r];
-  const bool valid = id >= 0 && id < V;
-  const size_t base = valid ? static_cast<size_t>(id) * H : 0;
-  double ss = 0.0;
-  for (int c = threadIdx.x * 8; c < H; c += blockDim.x * 8) {
-    u32x4 v = valid ? *reinterpret_cast<const u32x4*>(E + base + c) : u32x4{0u, 0u, 0u, 0u};
-    float e[8];
+  const int c = threadIdx.x * 8;
+  const bool on = c < H;
+  if (EMBED)
+    for (int i = r * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = 0;
+  const int id = idx[r];
+  const bool valid = on && id >= 0 && id < n_src;
+  const size_t at = static_cast<size_t>(valid ? id : 0) * H + c;
+  float e[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  u32x4 gv = u32x4{0u, 0u, 0u, 0u};
+  if (on) gv = *reinterpret_cast<const u32x4*>(g + c);
+  if constexpr (EMBED) {
+    const u32x4 v = valid ? *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(src) + at)
+                          : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       e[2 * k] = bf2f(v[k] & 0xffffu);
       e[2 * k + 1] = bf2f(v[k] >> 16);
     }
-    float4* dst = reinterpret_cast<float4*>(x + static_cast<size_t>(r) * H + c);
-    dst[0] = make_float4(e[0], e[1], e[2], e[3]);
-    dst[1] = make_float4(e[4], e[5], e[6], e[7]);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) ss += static_cast<double>(e[k]) * e[k];
+    if (on) {
+      float4* dst = reinterpret_cast<float4*>(x + static_cast<size_t>(r) * H + c);
+      dst[0] = make_float4(e[0], e[1], e[2], e[3]);
+      dst[1] = make_float4(e[4], e[5], e[6], e[7]);
+    }
+  } else if (valid) {
+    const float4* v = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + at);
+    const float4 lo = v[0], hi = v[1];
+    e[0] = lo.x; e[1] = lo.y; e[2] = lo.z; e[3] = lo.w;
+    e[4] = hi.x; e[5] = hi.y; e[6] = hi.z; e[7] = hi.w;
   }
-  // whole-row sum of x^2 in a fixed order: one partial per row
+  double ss = 0.0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) ss += static_cast<double>(e[k]) * e[k];
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
   if ((threadIdx.x & 63) == 0) s_ss[threadIdx.x >> 6] = ss;
   __syncthreads();
-  if (threadIdx.x == 0) ssq[r] = (s_ss[0] + s_ss[1]) + (s_ss[2] + s_ss[3]);
+  double tot = 0.0;
+  for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) tot += s_ss[w];
+  const double rr = 1.0 / sqrt(tot / static_cast<double>(H) + static_cast<double>(eps));
+  if (!on) return;
+  u32x4 o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    o[k] = d2bf(static_cast<double>(e[2 * k]) * bf2f(gv[k] & 0xffffu) * rr) |
+           (d2bf(static_cast<double>(e[2 * k + 1]) * bf2f(gv[k] >> 16) * rr) << 16);
+  *reinterpret_cast<u32x4*>(hg + frag_index(r, c, Rg)) = o;
 }
 
-hipError_t launch_embed(const uint16_t* E, const int32_t* ids, int R, int H, int V, float* x, double* ssq,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_embed, dim3(R), dim3(256), 0, s, E, ids, H, V, x, ssq);
+hipError_t launch_embed_norm(const uint16_t* E, const int32_t* ids, int R, int H, int V, float* x, const uint16_t* g,
+                             float eps, uint16_t* hg, int Rg, int* zero, int n_zero, hipStream_t s) {
+  if (H % 8 != 0 || H > 8192) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_first_norm<true>, dim3(R), dim3((H / 8 + 63) / 64 * 64), 0, s, E, ids, V, H, x, g, eps, hg, Rg,
+                     zero, n_zero);
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- row gather
-// Compact the residual rows that return logits (a prefill pass asks for a
-// few rows out of many) with each row's sum of x^2 (one partial per row, in
-// a fixed order).  Indices outside [0, R_in) give a zero row.
-__global__ __launch_bounds__(256) void k_gather_rows(const float* __restrict__ x_in, int R_in,
-                                                     const int32_t* __restrict__ rows, int H,
-                                                     float* __restrict__ x_out, double* __restrict__ ssq_out) {
-  __shared__ double s_ss[4];
-  const int i = blockIdx.x;
-  const int src = rows[i];
-  const bool valid = src >= 0 && src < R_in;
-  double ss = 0.0;
-  for (int c = threadIdx.x * 4; c < H; c += blockDim.x * 4) {
-    const float4 v = valid ? *reinterpret_cast<const float4*>(x_in + static_cast<size_t>(src) * H + c)
-                           : make_float4(0.f, 0.f, 0.f, 0.f);
-    *reinterpret_cast<float4*>(x_out + static_cast<size_t>(i) * H + c) = v;
-    ss += static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y + static_cast<double>(v.z) * v.z +
-          static_cast<double>(v.w) * v.w;
-  }
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
-  if ((threadIdx.x & 63) == 0) s_ss[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  if (threadIdx.x == 0) ssq_out[i] = (s_ss[0] + s_ss[1]) + (s_ss[2] + s_ss[3]);
-}
-
-hipError_t launch_gather_rows(const float* x_in, int R_in, const int32_t* rows, int Ro, int H, float* x_out,
-                              double* ssq_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_gather_rows, dim3(Ro), dim3(256), 0, s, x_in, R_in, rows, H, x_out, ssq_out);
+hipError_t launch_gather_norm(const float* x, int R_in, const int32_t* rows, int Ro, int H, const uint16_t* g,
+                              float eps, uint16_t* hg, int Rg, hipStream_t s) {
+  if (H % 8 != 0 || H > 8192) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_first_norm<false>, dim3(Ro), dim3((H / 8 + 63) / 64 * 64), 0, s, x, rows, R_in, H, nullptr, g,
+                     eps, hg, Rg, nullptr, 0);
   return hipGetLastError();
 }
 

@@ -5,10 +5,13 @@
 
 namespace vsk {
 
-hipError_t launch_embed(const uint16_t* E, const int32_t* ids, int R, int H, int V, float* x, double* ssq,
-                        hipStream_t s);
-hipError_t launch_gather_rows(const float* x_in, int R_in, const int32_t* rows, int Ro, int H, float* x_out,
-                              double* ssq_out, hipStream_t s);
+// x = the embedding rows of ids and their first attention norm as frags; also
+// clears n_zero words at `zero` (nullable)
+hipError_t launch_embed_norm(const uint16_t* E, const int32_t* ids, int R, int H, int V, float* x, const uint16_t* g,
+                             float eps, uint16_t* hg, int Rg, int* zero, int n_zero, hipStream_t s);
+// the final norm of the listed rows of the residual stream, as frags
+hipError_t launch_gather_norm(const float* x, int R_in, const int32_t* rows, int Ro, int H, const uint16_t* g,
+                              float eps, uint16_t* hg, int Rg, hipStream_t s);
 // Where a normalised row goes in a routed layer: mask non-null puts row r at
 // its cohort position inv[r], in the RUN buffer (the norm's own output) when
 // mask[r] != 0 and in `po` otherwise.  A null mask keeps row r at row r.
