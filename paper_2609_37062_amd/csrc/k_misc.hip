@@ -9,6 +9,30 @@
 
 namespace vsk {
 
+// ---------------------------------------------------------------- rows to XCDs
+// A norm writes its row as 16-byte pieces of frags whose 128-byte lines hold
+// eight rows.  Workgroups go to the 8 XCDs in turn: in row order the eight rows
+// of a line are written through eight L2s, as eight partial lines.  From
+// kXcdRows rows on, all 16 rows of a group go to one XCD (a group to each XCD
+// in turn), and its L2 completes the lines: 2,080 rows of k_rmsnorm_frags 15.1
+// -> 12.5 us, k_first_norm 21.4 -> 18.3, k_resid_norm<2> of 777 rows of 4,096
+// 15.0 -> 13.7.  (Fewer rows would
+// leave XCDs idle.)
+constexpr int kXcdRows = 128;
+struct RowPart {
+  int row, part;
+};
+__device__ __forceinline__ RowPart xcd_row(int R, int parts) {
+  const int bid = blockIdx.x;
+  if (R < kXcdRows) return RowPart{bid / parts, bid % parts};
+  const int slot = bid >> 3, per = 16 * parts;
+  const int rem = slot % per;
+  return RowPart{((slot / per) * 8 + (bid & 7)) * 16 + rem % 16, rem / 16};
+}
+static int xcd_grid(int R, int parts) {  // (rows past R exit at once)
+  return (R < kXcdRows ? R : (R + 127) / 128 * 128) * parts;
+}
+
 // ---------------------------------------------------------------- first and last norm
 // The rows a norm of a pass starts from, and that norm, one workgroup per row
 // and one thread per 8 columns: x[r] = float(E[ids[r]]) and the first layer's
@@ -24,14 +48,15 @@ template <bool EMBED>
 __global__ __launch_bounds__(1024) void k_first_norm(const void* __restrict__ src, const int32_t* __restrict__ idx,
                                                      int n_src, int H, float* __restrict__ x,
                                                      const uint16_t* __restrict__ g, float eps,
-                                                     uint16_t* __restrict__ hg, int Rg, int* __restrict__ zero,
-                                                     int n_zero) {
+                                                     uint16_t* __restrict__ hg, int R, int Rg,
+                                                     int* __restrict__ zero, int n_zero) {
   __shared__ double s_ss[16];
-  const int r = blockIdx.x;
+  const int r = xcd_row(R, 1).row;
+  if (r >= R) return;
   const int c = threadIdx.x * 8;
   const bool on = c < H;
   if (EMBED)
-    for (int i = r * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = 0;
+    for (int i = r * blockDim.x + threadIdx.x; i < n_zero; i += R * blockDim.x) zero[i] = 0;
   const int id = idx[r];
   const bool valid = on && id >= 0 && id < n_src;
   const size_t at = static_cast<size_t>(valid ? id : 0) * H + c;
@@ -79,16 +104,16 @@ __global__ __launch_bounds__(1024) void k_first_norm(const void* __restrict__ sr
 hipError_t launch_embed_norm(const uint16_t* E, const int32_t* ids, int R, int H, int V, float* x, const uint16_t* g,
                              float eps, uint16_t* hg, int Rg, int* zero, int n_zero, hipStream_t s) {
   if (H % 8 != 0 || H > 8192) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_first_norm<true>, dim3(R), dim3((H / 8 + 63) / 64 * 64), 0, s, E, ids, V, H, x, g, eps, hg, Rg,
-                     zero, n_zero);
+  hipLaunchKernelGGL(k_first_norm<true>, dim3(xcd_grid(R, 1)), dim3((H / 8 + 63) / 64 * 64), 0, s, E, ids, V, H, x, g,
+                     eps, hg, R, Rg, zero, n_zero);
   return hipGetLastError();
 }
 
 hipError_t launch_gather_norm(const float* x, int R_in, const int32_t* rows, int Ro, int H, const uint16_t* g,
                               float eps, uint16_t* hg, int Rg, hipStream_t s) {
   if (H % 8 != 0 || H > 8192) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_first_norm<false>, dim3(Ro), dim3((H / 8 + 63) / 64 * 64), 0, s, x, rows, R_in, H, nullptr, g,
-                     eps, hg, Rg, nullptr, 0);
+  hipLaunchKernelGGL(k_first_norm<false>, dim3(xcd_grid(Ro, 1)), dim3((H / 8 + 63) / 64 * 64), 0, s, x, rows, R_in, H,
+                     nullptr, g, eps, hg, Ro, Rg, nullptr, 0);
   return hipGetLastError();
 }
 
@@ -106,8 +131,10 @@ hipError_t launch_gather_norm(const float* x, int R_in, const int32_t* rows, int
 __global__ __launch_bounds__(64) void k_rmsnorm_frags(const float* __restrict__ x, const uint16_t* __restrict__ g,
                                                       const double* __restrict__ ssq, int parts, int R, int H,
                                                       float eps, uint16_t* __restrict__ hg, int Rg, CohortOut rc) {
-  const int r = blockIdx.y;
-  const int c = blockIdx.x * 512 + threadIdx.x * 8;
+  const RowPart rp = xcd_row(R, (H + 511) / 512);
+  const int r = rp.row;
+  if (r >= R) return;
+  const int c = rp.part * 512 + threadIdx.x * 8;
   const bool on = c < H;
   const float* xr = x + static_cast<size_t>(r) * H;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
@@ -166,7 +193,8 @@ __global__ __launch_bounds__(1024) void k_resid_norm(float* __restrict__ x, cons
   if constexpr (NS > 0) splits = NS;
   constexpr int kMax = NS > 0 ? NS : kResidNormMaxSplits;
   __shared__ double s_ss[16];
-  const int r = blockIdx.x;
+  const int r = xcd_row(R, 1).row;
+  if (r >= R) return;
   const int c = threadIdx.x * 8;
   const bool on = c < H;
   float* xr = x + static_cast<size_t>(r) * H + c;
@@ -231,19 +259,19 @@ hipError_t launch_resid_norm(float* x, const float* y, int splits, int R, int H,
   if (H % 8 != 0 || H > 8192 || splits < 1 || splits > kResidNormMaxSplits) return hipErrorInvalidValue;
   const int threads = (H / 8 + 63) / 64 * 64;
   switch (splits) {
-    case 2: hipLaunchKernelGGL(k_resid_norm<2>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
-    case 3: hipLaunchKernelGGL(k_resid_norm<3>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
-    case 4: hipLaunchKernelGGL(k_resid_norm<4>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
-    case 5: hipLaunchKernelGGL(k_resid_norm<5>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
-    case 8: hipLaunchKernelGGL(k_resid_norm<8>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
-    default: hipLaunchKernelGGL(k_resid_norm<0>, dim3(R), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc);
+    case 2: hipLaunchKernelGGL(k_resid_norm<2>, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    case 3: hipLaunchKernelGGL(k_resid_norm<3>, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    case 4: hipLaunchKernelGGL(k_resid_norm<4>, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    case 5: hipLaunchKernelGGL(k_resid_norm<5>, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    case 8: hipLaunchKernelGGL(k_resid_norm<8>, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc); break;
+    default: hipLaunchKernelGGL(k_resid_norm<0>, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y, splits, R, H, g, eps, hg, Rg, rc);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_rmsnorm_frags(const float* x, const uint16_t* g, const double* ssq, int parts, int R, int H,
                                 float eps, uint16_t* hg, int Rg, hipStream_t s, CohortOut rc) {
-  hipLaunchKernelGGL(k_rmsnorm_frags, dim3((H + 511) / 512, R), dim3(64), 0, s, x, g, ssq, parts, R, H, eps, hg, Rg,
+  hipLaunchKernelGGL(k_rmsnorm_frags, dim3(xcd_grid(R, (H + 511) / 512)), dim3(64), 0, s, x, g, ssq, parts, R, H, eps, hg, Rg,
                      rc);
   return hipGetLastError();
 }
@@ -322,7 +350,8 @@ __global__ __launch_bounds__(1024) void k_route_reduce_norm(float* __restrict__ 
                                                             const uint16_t* __restrict__ g, float eps,
                                                             uint16_t* __restrict__ hg, int Rg) {
   __shared__ double s_ss[16];
-  const int r = blockIdx.x;
+  const int r = xcd_row(R, 1).row;
+  if (r >= R) return;
   const int c = threadIdx.x * 8;
   const bool on = c < H;
   const bool is_run = mask[r] != 0;
@@ -388,7 +417,7 @@ hipError_t launch_route_reduce_norm(float* x, const float* y_run, int s_run, con
       s_po > kResidNormMaxSplits)
     return hipErrorInvalidValue;
   const int threads = (H / 8 + 63) / 64 * 64;
-  hipLaunchKernelGGL(k_route_reduce_norm, dim3(R), dim3(threads), 0, s, x, y_run, s_run, y_po, s_po, mask, inv, wts,
+  hipLaunchKernelGGL(k_route_reduce_norm, dim3(xcd_grid(R, 1)), dim3(threads), 0, s, x, y_run, s_run, y_po, s_po, mask, inv, wts,
                      R, H, g, eps, hg, Rg);
   return hipGetLastError();
 }
