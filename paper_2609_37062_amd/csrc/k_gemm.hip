@@ -633,6 +633,28 @@ GemmPlan plan_gemm(int N, int K, int R, int epi, int shape, int resid_target, in
         p.wn = 8;
         wk = 1;
       }
+      // gate/up or a head of few columns (a projector, a narrow model, a small
+      // vocabulary): so many tiles per workgroup would leave most compute
+      // units idle.  A workgroup's time goes with the KiB it moves per K step,
+      // 8 of X and one per tile, so of 16, 8, 4 and 2 tiles the least rounds x
+      // that (8B projector, 1792 columns, 256 rows: 14 workgroups 54.6 us, 112
+      // of two tiles 25.2; 3B gate/up at 200 rows: 128 workgroups 45.9, 256 of
+      // eight tiles 33.3).
+      if (auto_shape && wide_n) {
+        const int nt_all = N / 16;
+        auto wgs = [&](int tn) { return (nt_all + tn - 1) / tn * p.m_tiles; };
+        auto cost = [&](int tn) { return (wgs(tn) + kComputeUnits - 1) / kComputeUnits * (8 + tn); };
+        const int widest = p.nt * p.wn;
+        int tn = widest;
+        if (wgs(widest) <= kRowTiledSplitBelow)
+          for (const int t : {8, 4, 2})
+            if (t < widest && cost(t) < cost(tn)) tn = t;
+        if (tn < widest) {
+          p.wn = tn == 2 ? 2 : 4;
+          p.nt = tn / p.wn;
+          wk = 8 / p.wn;
+        }
+      }
     } else if (auto_shape && !one_tile && p.mg == 8 && epi == EPI_QKV) {
       // QKV of a row-tiled pass: X in LDS, eight waves side by side with one
       // N tile each (two per wave compile without spills but measured slower

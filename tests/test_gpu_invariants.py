@@ -125,6 +125,23 @@ def test_integer_inputs_bit_exact_row_tiled(variant, rows):
     d.release()
 
 
+@pytest.mark.parametrize("rows", [136, 600, 1150])
+def test_integer_inputs_bit_exact_row_tiled_few_columns(rows):
+    """Row-tiled gate/up of few columns in workgroups of 2, 4 and 8 column
+    tiles (MID's 192 tiles at 2, 5 and 9 row tiles), bit for bit."""
+    m = MID
+    w = fresh_workload(m, rows, seed=rows, name=f"int-narrow-r{rows}")
+    over = int_overrides(m, "mlp", seed=rows)
+    d = _device(w, overrides=over)
+    d.step()
+    d.results()
+    x_dev = d.residual()
+    a, batch, sub, r, kv, idx = oracle_state(w)
+    out = forward(m, GeneratedWeights(m, w.seed, overrides=over), kv, sub, w.tokens[r], None, want_hidden=True)
+    np.testing.assert_array_equal(x_dev, out["x"])
+    d.release()
+
+
 # 17..64 rows: gate/up in 128-column workgroups, the head in 256-column ones
 # (the last one ragged), K of 34 and 258 steps split unevenly over workgroups
 WIDE = ModelCfg("wide-2L", n_layers=2, hidden=1088, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=8256,
