@@ -506,13 +506,17 @@ static hipError_t launch_ntw(const GemmArgs& a_in, int m_tiles, int ksplit, hipS
 // stream from displacing what the L2 holds (a pure stream of 235 MB in this
 // order 46.6 -> 43.2 us; the batch-1 pass of four 3B layers and the head 407
 // -> 371 us, batch 128 of four 8B layers 1135 -> 1089).  Row tiles share
-// weight tiles through the L2: ordinary loads.
+// weight tiles through the L2: ordinary loads.  So do residual and QKV
+// projections of 65 to 128 rows below 64 MiB of weights (QKV at 100 and 128
+// rows of the 3B and 8B shapes 14.8 and 20.0 us non-temporal, 13.1 and 18.9
+// not; O and down of the 3B 15.0 and 14.2; with the 8B down 22.2 and 22.7).
 template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL = false>
 static hipError_t launch_cfg(const GemmArgs& a, int m_tiles, int ksplit, hipStream_t s, const LaunchEvents& ev) {
   constexpr bool kOneTile = MG == 1 || MG == 4;    // never row-tiled
   constexpr bool kRowTiled = MG == 6 || MG == 7 || MG == 11;  // heights of row-tiled passes
   if constexpr (!kOneTile)
-    if (kRowTiled || m_tiles > 1) return launch_ntw<MG, NT, WN, WK, PF, EPI, XL, false>(a, m_tiles, ksplit, s, ev);
+    if (kRowTiled || m_tiles > 1 || (EPI == EPI_RESID && static_cast<size_t>(a.N) * a.Kt < (1u << 20)))
+      return launch_ntw<MG, NT, WN, WK, PF, EPI, XL, false>(a, m_tiles, ksplit, s, ev);
   if constexpr (!kRowTiled) return launch_ntw<MG, NT, WN, WK, PF, EPI, XL, true>(a, m_tiles, ksplit, s, ev);
   return hipErrorInvalidValue;
 }
