@@ -1055,8 +1055,8 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   // in all (8B, 100 rows of 1,500 to 2,500 tokens: 1,202 us for four layers at
   // 96 blocks a split, 1,114 uncut).
   const int pairs = n_dec * c.n_kv_heads;
-  if (h.attn_bps == 0 && ((pairs >= 128 && pairs < 256 && 5 * blk_min >= 4 * blk_max) ||
-                          blk_sum * c.n_kv_heads >= static_cast<int64_t>(kAttnSlots) * blk_max))
+  if (h.attn_bps == 0 && n_dec > 0 && ((pairs >= 128 && pairs < 256 && 5 * blk_min >= 4 * blk_max) ||
+                                       blk_sum * c.n_kv_heads >= static_cast<int64_t>(kAttnSlots) * blk_max))
     aa.bps = std::clamp((blk_max + 7) / 8 * 8, kAttnMinBps, kAttnMaxBps);
   aa.max_splits = attn_splits(b.max_kv_len, aa.bps);
   aa.part_o = reinterpret_cast<float*>(ws + wl.att_o);

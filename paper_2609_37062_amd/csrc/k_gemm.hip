@@ -526,8 +526,9 @@ static hipError_t launch_cfg(const GemmArgs& a, int m_tiles, int ksplit, hipStre
 //          flight (residual projections: N = hidden);
 //  pair    two N tiles per wave, 4 K steps in flight (QKV, gate/up);
 //  wide    four N tiles per wave (lm_head).
-// For 2..8 row groups (2 takes the 4-row-group layouts) the default
-// (shape 0) is, with one row tile: X staged
+// For 2..4 row groups the default (shape 0) is k_gemm_tiled; the layouts of 4
+// row groups here are what shapes 1..6 select.  For 5..8 row groups (and
+// shape 6 at 4) it is, with one row tile: X staged
 // in LDS by a ninth wave for gate/up (four N tiles; at 8 row groups eight,
 // two per wave) and lm_head (sixteen, two per wave, the eight waves side by
 // side), for the residual projections and QKV the four-tile (4 row groups)
@@ -600,9 +601,8 @@ GemmPlan plan_gemm(int N, int K, int R, int epi, int shape, int resid_target, in
   const int Rg = (R + 15) / 16;
   if (shape == 0 && Rg > 1 && Rg <= kTiledGroups)
     return plan_tiled(N, K, R, epi, resid_target < 0 ? 0 : resid_target > 0 ? resid_target : kTiledTargetWgs);
-  // 17..32 rows take the 4-row-group layouts (the padding groups re-read the
-  // last one): against one column of K-split waves over 2 row groups the 8B
-  // step at 24 and 32 rows went from 5.15 / 5.24 to 4.58 / 4.67 ms
+  // (17..32 rows take the 4-row-group layouts, the padding groups re-reading
+  // the last one)
   p.mg = Rg <= 1 ? 1 : Rg <= 4 ? 4 : 8;
   p.m_tiles = (Rg + p.mg - 1) / p.mg;
   p.nt = 1;
