@@ -68,8 +68,8 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   constexpr int kBuf = tiled_buffers(MG, TN);
   constexpr int kLead = kBuf - 1;          // chunks copied ahead
   constexpr int kStep = MG + TN;           // 1 KiB fragments per K step
-  constexpr int kPieces = kChunk * kStep;      // and per chunk
-  constexpr int kCopies = (kPieces + 7) / 8;     // copies per wave and chunk, one fewer for waves kFull..
+  constexpr int kPieces = kChunk * kStep;  // and per chunk
+  constexpr int kCopies = (kPieces + 7) / 8;  // copies per wave and chunk, one fewer for waves kFull..
   constexpr int kFull = kPieces - 8 * (kCopies - 1);
   constexpr int XB = (MGW + 1) / 2;        // row groups of the first half step
   static_assert(MG % WM == 0 && kBuf >= 2 && (kLead - 1) * kCopies <= 63, "outstanding loads beyond the wait counter");
@@ -120,8 +120,9 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
       if (q < MG)
         lds_copy16<false>(a.X + (static_cast<size_t>(kt + st) * a.Rg + min(q, a.Rg - 1)) * 64, voff, dst + p * 8192);
       else
-        lds_copy16<true>(a.W + (static_cast<size_t>(min(ng * TN + q - MG, n_tiles - 1)) * w_stride(a.Kt) + kt + st) * 64, voff,
-                        dst + p * 8192);
+        lds_copy16<true>(
+            a.W + (static_cast<size_t>(min(ng * TN + q - MG, n_tiles - 1)) * w_stride(a.Kt) + kt + st) * 64, voff,
+            dst + p * 8192);
     }
   };
   // wait until this wave's copies of all but the newest kLead - 1 chunks have landed
@@ -133,7 +134,6 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   const u32x4* ws = reinterpret_cast<const u32x4*>(smem) + (MG + wn * NT) * 64 + lane;
   u32x4 xa[XB], xb[XB], wa[NT], wb[NT];
   // X fragments of the first (h = 0) or second half of a step's row groups
-  // (a short wave reads past its groups: the next piece, never multiplied)
   auto xread = [&](u32x4 (&r)[XB], int c, int st, auto h_c) {
     constexpr int h = decltype(h_c)::value;
     const u32x4* p = xs + ((c % kBuf) * kPieces + st * kStep + h * XB) * 64;
