@@ -490,7 +490,7 @@ __global__ __launch_bounds__(1024) void k_argmax_logits(const void* __restrict__
   typedef std::conditional_t<DT == 0, uint16_t, float> T;
   constexpr int VE = 16 / sizeof(T);  // logits per load
   constexpr int kU = 4;               // loads in flight
-  __shared__ int s_first;
+  __shared__ int s_found;
   const int r = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const T* row = reinterpret_cast<const T*>(logits) + static_cast<size_t>(r) * vocab;
   auto value = [&](int j) -> float {
@@ -543,20 +543,16 @@ __global__ __launch_bounds__(1024) void k_argmax_logits(const void* __restrict__
   for (int k = 0; k < VE; ++k)
     if (mi[k] >= 0) am_merge(bv, bi, mv[k], head + mi[k] * VE + k);
   block_am_reduce(bv, bi);
-  if (tid == 0) s_first = bi;
+  if (tid == 0) s_found = bi;
   __syncthreads();
-  bi = s_first;
-  if (bi == INT_MAX) {  // (uniform) nothing above -inf: the first value that is not NaN
-    bool found = false;
-    for (int j = tid; j < vocab && !found; j += nt) {
+  if (s_found == INT_MAX) {  // (uniform: written once, above) nothing above -inf: the first value that is not NaN
+    bv = -INFINITY;
+    bi = INT_MAX;
+    for (int j = tid; j < vocab && bi == INT_MAX; j += nt) {
       const float v = value(j);
-      if (v == v) {
-        atomicMin(&s_first, j);
-        found = true;
-      }
+      if (v == v) bi = j;
     }
-    __syncthreads();
-    bi = s_first;
+    block_am_reduce(bv, bi);
   }
   if (tid == 0) {
     ids[r] = (bi == INT_MAX) ? 0 : bi;

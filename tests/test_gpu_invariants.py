@@ -424,6 +424,36 @@ def test_argmax_sample_unaligned_rows(dtype, vocab, offset):
     np.testing.assert_array_equal(ids.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("vocab", [128256, 4099, 1030, 70])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_argmax_sample_rows_without_a_value_above_minus_inf(dtype, vocab):
+    """Fully masked rows (-inf, NaN mixed in) return their first value that is
+    not NaN, wherever each wave of the row's workgroup finds its own first one;
+    twenty calls, every one the same."""
+    from paper_2609_37062_amd import vsk
+    rng = np.random.default_rng(vocab)
+    rows = 512
+    first = np.minimum(vocab - 1, np.concatenate([np.array([0, 1, 63, 64, 960, 1023, 1024, vocab - 1]),
+                                                  rng.integers(0, vocab, size=rows - 9), [vocab]]))
+    z = torch.full((rows, vocab), float("-inf"), dtype=dtype, device="cuda")
+    j = torch.arange(vocab, device="cuda")[None, :]
+    z.masked_fill_(j < torch.from_numpy(first).cuda()[:, None], float("nan"))
+    z[:, first.max() // 2:].masked_fill_(torch.rand((rows, vocab - first.max() // 2), device="cuda") < 0.5, float("nan"))
+    z[torch.arange(rows), torch.from_numpy(first).cuda()] = float("-inf")
+    z[-1] = float("nan")
+    want = np.append(first[:-1], 0)
+    ids = torch.empty(rows, dtype=torch.int32, device="cuda")
+    none = torch.empty(rows, dtype=torch.int32, device="cuda")
+    print(f"[gpu] argmax_sample masked rows {dtype} vocab={vocab}", flush=True)
+    for _ in range(20):
+        ids.fill_(-7)
+        none.fill_(-7)
+        vsk.argmax_sample(z.data_ptr(), 0 if dtype == torch.bfloat16 else 1, rows, vocab, ids.data_ptr(),
+                          torch.cuda.current_stream().cuda_stream, none.data_ptr())
+        np.testing.assert_array_equal(ids.cpu().numpy(), want)
+        np.testing.assert_array_equal(none.cpu().numpy(), np.append(np.zeros(rows - 1, np.int32), 1))
+
+
 def test_argmax_sample_rejects_bad_arguments():
     from paper_2609_37062_amd import vsk
     t = torch.zeros((2, 8), dtype=torch.float32, device="cuda")
