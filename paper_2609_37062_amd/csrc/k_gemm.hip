@@ -643,8 +643,9 @@ GemmPlan plan_gemm(int N, int K, int R, int epi, int shape, int resid_target, in
       // 8 of X and one per tile, so of 16, 8, 4 and 2 tiles the least rounds x
       // that (8B projector, 1792 columns, 256 rows: 14 workgroups 54.6 us, 112
       // of two tiles 25.2; 3B gate/up at 200 rows: 128 workgroups 45.9, 256 of
-      // eight tiles 33.3).
-      if (auto_shape && wide_n) {
+      // eight tiles 33.3).  A forced tile height keeps all 16: only they have
+      // the other heights.
+      if (auto_shape && wide_n && row_tile == 0) {
         const int nt_all = N / 16;
         auto wgs = [&](int tn) { return (nt_all + tn - 1) / tn * p.m_tiles; };
         auto cost = [&](int tn) { return (wgs(tn) + kComputeUnits - 1) / kComputeUnits * (8 + tn); };

@@ -1,0 +1,44 @@
+"""The projection planner of the built library (plan_gemm), called on the CPU:
+what a forced tile height (tuning key 10) gives over the sizes it is accepted
+for."""
+import ctypes
+
+import pytest
+
+from paper_2609_37062_amd import vsk
+
+RESID, QKV, SWIGLU, LOGITS = range(4)
+
+
+class Plan(ctypes.Structure):
+    """GemmPlan (csrc/gemm.hpp)."""
+    _fields_ = [(n, ctypes.c_int) for n in ("mg", "m_tiles", "n_groups", "nt", "wn", "ksplit")] + \
+        [("tiled", ctypes.c_bool), ("xl", ctypes.c_bool)]
+
+
+def plan(N, K, R, epi, shape=0, resid_target=0, row_tile=0):
+    f = vsk.lib()._ZN3vsk9plan_gemmEiiiiiii
+    f.restype, f.argtypes = Plan, [ctypes.c_int] * 7
+    return f(N, K, R, epi, shape, resid_target, row_tile)
+
+
+@pytest.mark.parametrize("row_tile", [6, 7, 8, 11])
+@pytest.mark.parametrize("rows", [129, 200, 405, 777, 2080])
+@pytest.mark.parametrize("N,K", [(3072, 512), (4096, 1024), (1792, 4096), (16384, 3072), (28672, 4096)])
+def test_forced_tile_height(N, K, rows, row_tile):
+    """Key 10 forces the height of the gate/up tiles, however few the columns:
+    eight waves side by side over 16 column tiles, as it is for wide ones."""
+    p = plan(N, K, rows, SWIGLU, row_tile=row_tile)
+    rg = (rows + 15) // 16
+    assert p.xl and (p.mg, p.wn, p.nt) == (row_tile, 8, 2)
+    assert (p.m_tiles, p.n_groups) == (-(-rg // row_tile), -(-N // 256))
+
+
+@pytest.mark.parametrize("N,K,rows,tiles", [(3072, 512, 136, 2), (3072, 512, 600, 4), (3072, 512, 1150, 8),
+                                            (1792, 4096, 256, 2), (16384, 3072, 200, 8), (28672, 4096, 777, 16)])
+def test_automatic_gate_up_workgroups(N, K, rows, tiles):
+    """Without key 10, gate/up of few columns takes narrower workgroups."""
+    p = plan(N, K, rows, SWIGLU)
+    assert p.nt * p.wn == tiles
+    if tiles < 16:
+        assert p.mg == 8
