@@ -104,6 +104,13 @@ struct PTerms {
 // column's maximum moved.  Prefill attention of 1,000 rows at 4,104 cached
 // tokens (3B-class layer): 289 -> 182 us; shared prefix of 64 sequences 12.9 ->
 // 10.7 us, their own keys after it 14.9 -> 13.4 us.
+//
+// The fma takes the product unrounded and mb is the maximum's product rounded,
+// so the maximum's exponent is not 0 but up to half an ulp of mb away: nothing
+// for ordinary scores, 128 (and the probabilities infinite or all flushed) at
+// 2^31.  From kRoundedScores on, where half an ulp is 1/2, the product is
+// rounded first.
+constexpr float kRoundedScores = 0x1p23f;
 template <int D, bool MASK, bool FULL>
 __device__ __forceinline__ void pair_scores(const u32x4 (&qf)[D / 32], const u32x4 (&kg)[2][D / 32], int t0,
                                             int t_end, int lim, float sc, float& m, float& l, PTerms& pp,
@@ -132,10 +139,21 @@ __device__ __forceinline__ void pair_scores(const u32x4 (&qf)[D / 32], const u32
   // below 2^-126 (flushed to 0) is negligible beside the maximum's 1
   alpha = __builtin_amdgcn_exp2f(m - mb);
   float p[8], ps[2] = {0.f, 0.f};
+  if (__any(fabsf(mb) >= kRoundedScores)) {
+    // both sides of the difference rounded alike, so the maximum's is 0
+#pragma clang fp contract(off)
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    p[r] = __builtin_amdgcn_exp2f(fmaf(s0[r], sc, -mb));
-    p[4 + r] = __builtin_amdgcn_exp2f(fmaf(s1[r], sc, -mb));
+    for (int r = 0; r < 4; ++r) {
+      const float a = s0[r] * sc, b = s1[r] * sc;
+      p[r] = __builtin_amdgcn_exp2f(a - mb);
+      p[4 + r] = __builtin_amdgcn_exp2f(b - mb);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(fmaf(s0[r], sc, -mb));
+      p[4 + r] = __builtin_amdgcn_exp2f(fmaf(s1[r], sc, -mb));
+    }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {

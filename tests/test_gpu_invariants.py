@@ -274,6 +274,44 @@ def test_zero_queries_average_v():
     d.release()
 
 
+@pytest.mark.parametrize("scale", [2.0 ** 20, 2.0 ** 30, 2.0 ** 60, 2.0 ** 100])
+@pytest.mark.parametrize("kind", ["decode", "shared", "mixed"])
+def test_huge_scores_pick_the_largest(kind, scale):
+    """Cached keys scaled far up: scores of 2^20 and more, up to 2^100, whose
+    softmax is one-hot at the largest (no two of the drawn ones are within
+    float32 rounding of each other), so every output is one key's V.  Through
+    the decode walk (one split and merged splits), the shared prefix's and the
+    prompt rows'; against the oracle within one bf16 ulp."""
+    m = TINY
+    rng = np.random.default_rng(6)
+    if kind == "decode":
+        w = decode_workload(m, rng.integers(40, 600, size=8), seed=6, name="huge-decode")
+    elif kind == "shared":
+        w = decode_workload(m, 256 + rng.integers(1, 90, size=8), seed=6, shared=256, name="huge-shared")
+    else:
+        w = mixed_workload(m, n_pre=1, plen=40, ctx=rng.integers(40, 300, size=4), seed=6, name="huge-mixed")
+    over = {("embed", -1): np.ones((m.vocab, m.hidden)), ("wo", 0): np.eye(m.hidden),
+            ("w_down", 0): np.zeros((m.hidden, m.ffn))}
+    if kind == "mixed":  # the prompt's own keys are what its rows attend to
+        over[("wk", 0)] = scale * rng.choice([-1.0, 1.0], size=(m.kv_dim, m.hidden)) / 64
+    d = _device(w, overrides=over)
+    a, batch, sub, r, kv, idx = oracle_state(w)
+    slots = _cached_slots(d, w)
+    K, V = d.read_kv(0, slots)
+    _write_kv(d, 0, slots, K * scale, V)
+    kv.write(0, slots, K * scale, V)
+    W = GeneratedWeights(m, w.seed, overrides=over)
+    o_or = forward(m, W, kv, sub, w.tokens[r], None)["x"] - 1.0
+    ulp = np.exp2(np.floor(np.log2(np.maximum(np.abs(o_or), 2.0 ** -8))) - 7)
+    for bps in (0, 8):
+        d.eng.set_tuning(0, bps)
+        d.step()
+        o_dev = d.residual() - 1.0
+        assert np.isfinite(o_dev).all(), (bps, int((~np.isfinite(o_dev)).sum()))
+        assert np.all(np.abs(o_dev - o_or) <= ulp), (bps, np.abs(o_dev - o_or).max())
+    d.release()
+
+
 def test_first_token_attends_to_itself_only():
     m = TINY
     w = fresh_workload(m, 6, seed=3, name="ctx0")
