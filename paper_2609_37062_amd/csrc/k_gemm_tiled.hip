@@ -16,7 +16,11 @@
 //    outstanding than it has issued since; the barrier then hands the chunk
 //    to all waves;
 //  * every wave multiplies the whole K range of its own tiles: no reduction
-//    across waves and no second pass over LDS;
+//    across waves and no second pass over LDS; even and odd K steps are summed
+//    apart, so a sum is no longer than one of the staged layout's, where two
+//    waves halve K (float32 sums of 37 rows, K of 4096, relative distance from
+//    a 64-bit product: 4.0e-7 in one sum, 2.7e-7 in two and in the staged
+//    layout; no time difference);
 //  * the fragments of the next half step are read while the current one
 //    multiplies, also across the barrier.
 // Measured (cold weights, us, staged -> here): gate/up 28672 x 4096 at 64 rows
@@ -96,11 +100,14 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   const int k_lo = ks * kc, k_hi = min(a.Kt, k_lo + kc);
   const int n_chunks = (k_hi - k_lo) / kChunk;
 
-  f32x4 acc[NT][MGW];
+  // one sum per step of a chunk, added at the end
+  f32x4 sums[kChunk][NT][MGW];
 #pragma unroll
-  for (int j = 0; j < NT; ++j)
+  for (int st = 0; st < kChunk; ++st)
 #pragma unroll
-    for (int g = 0; g < MGW; ++g) acc[j][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int g = 0; g < MGW; ++g) sums[st][j][g] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // This wave's copies of chunk c: pieces w, w + 8, ...; in each K step X
   // pieces first, then W.  Row groups and column tiles past the end copy a
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) r[j] = p[j * 64];
   };
-  auto mma = [&](const u32x4 (&fw)[NT], const u32x4 (&r)[XB], auto h_c) {
+  auto mma = [&](f32x4 (&acc)[NT][MGW], const u32x4 (&fw)[NT], const u32x4 (&r)[XB], auto h_c) {
     constexpr int h = decltype(h_c)::value;
 #pragma unroll
     for (int g = 0; g < XB; ++g) {
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
     if (st == 0) copy(c + kLead);
     xread(xb, c, st, kH1);
     __builtin_amdgcn_sched_barrier(0);
-    mma(wc, xa, kH0);
+    mma(sums[st], wc, xa, kH0);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (st == kChunk - 1) {
       wait_copies();
@@ -187,7 +194,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
       xread(xa, c, st + 1, kH0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    mma(wc, xb, kH1);
+    mma(sums[st], wc, xb, kH1);
     __builtin_amdgcn_sched_barrier(0);
   };
   static_assert(kChunk == 2, "two weight fragment sets, one per step of a chunk");
@@ -197,6 +204,11 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   }
   // the copies past the last step must land before the workgroup ends
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  f32x4 (&acc)[NT][MGW] = sums[0];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int g = 0; g < MGW; ++g) acc[j][g] += sums[1][j][g];
 
   // ---- epilogues
   if constexpr (EPI == EPI_RESID) {

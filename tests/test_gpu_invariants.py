@@ -181,6 +181,38 @@ def test_integer_inputs_bit_exact_17_to_64_rows(variant, rows, split):
     d.release()
 
 
+@pytest.mark.parametrize("target", [-1, 0])
+@pytest.mark.parametrize("hidden", [1024, 6144])
+@pytest.mark.parametrize("rows", [17, 37, 64])
+def test_float32_sums_of_17_to_64_rows(rows, hidden, target):
+    """Distance of the residual projections' float32 sums from a 64-bit product
+    of the same bf16 operands (fresh sequences, so O's input is the row's own
+    v, which vsk_kv_read returns): the default kernel, with K split (0) and
+    unsplit (-1), is no farther than the staged layout of key 3 = 4, whose
+    waves halve K.  Rounding errors of a running sum grow with the root of its
+    length, so one sum over the whole range is 1.41 times as far; the spread of
+    the ratio itself over rows x hidden outputs is below 2%."""
+    m = ModelCfg("sums", n_layers=1, hidden=hidden, n_q_heads=32, n_kv_heads=8, head_dim=128, ffn=64, vocab=1024)
+    w = fresh_workload(m, rows, seed=rows, name=f"sums-r{rows}-h{hidden}-t{target}")
+    d = _device(w, overrides={("w_down", 0): np.zeros((hidden, 64))})
+    wo, embed = d._tensor("wo", 0, (hidden, m.q_dim)), d._tensor("embed", -1, (m.vocab, hidden))
+    f64 = lambda t: t.view(torch.bfloat16).double()  # noqa: E731
+    err = {}
+    for shape in (0, 4):
+        d.eng.set_tuning(3, shape)
+        d.eng.set_tuning(5, target)
+        d.step()
+        _, V = d.read_kv(0, d.eng.batch_host()["slot"])
+        o = torch.from_numpy(np.repeat(V, m.n_q_heads // m.n_kv_heads, axis=1).reshape(rows, -1)).cuda()
+        y = (o @ f64(wo).t()).cpu().numpy()
+        x = f64(embed)[d.ids.long()].cpu().numpy() + y
+        err[shape] = np.linalg.norm(d.residual() - x) / np.linalg.norm(y)
+    print(f"[gpu] relative distance {err}", flush=True)
+    assert err[0] < 1e-6
+    assert err[0] <= 1.1 * err[4], err
+    d.release()
+
+
 # ---------------------------------------------------------------- attention invariants
 def _probe_overrides(m, v_row):
     """Embedding rows of ones (the normed input is exactly 1), Wv making every
