@@ -82,6 +82,9 @@ struct BatchHost {
   // Attention work of a pass with prefill rows (plan_prefill_items)
   std::vector<int32_t> pre_items;    // [n][3]: sequence, first row, rows -- runs of a sequence's new rows
   std::vector<int32_t> dec_rows;     // rows of one-row sequences, longest walk first
+  // blocks of the dec_rows' walks that an earlier one of them reads too: of
+  // walks after the shared prefix, and of whole walks (count_reread_blocks)
+  int64_t reread_own = 0, reread_all = 0;
   int32_t n_pre_items() const { return static_cast<int32_t>(pre_items.size() / 3); }
 };
 
@@ -93,6 +96,11 @@ struct BatchHost {
 // the decode grid dispatches its rows in that order, so the longest walks
 // start first instead of finishing last.
 void plan_prefill_items(BatchHost& b, int32_t group_size, int32_t block);
+
+// Count the blocks that the walks of one-row sequences read again
+// (reread_own, reread_all): a sequence against the first one whose walk starts
+// at the same block, as far as their tables agree.
+void count_reread_blocks(BatchHost& b, int32_t block);
 
 // Columns (row, query head) of one shared-prefix work item: 4 tiles of 16,
 // each walked by two waves; of one prefill work item: 8 tiles of 16.

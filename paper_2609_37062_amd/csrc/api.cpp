@@ -1030,7 +1030,8 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   const bool cascade = h.shared_prefix != 0 && b.n_pfx_items > 0 && pa.logit_rows == nullptr;
   // the blocks each row of the decode kernel walks (after its shared prefix)
   int blk_min = INT_MAX, blk_max = 0, n_dec = 0;
-  int64_t blk_sum = 0;
+  // and how many of those an earlier row of the launch reads too
+  int64_t blk_sum = 0, blk_again = 0;
   {
     const BatchHost& bh = h.bh;
     auto row_blocks = [&](int r) {
@@ -1040,12 +1041,25 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
       blk_sum += nb;
       ++n_dec;
     };
+    blk_again = cascade ? bh.reread_own : bh.reread_all;
     if (h.prefill_attn != 0 && b.n_pre_items > 0 && b.max_kv_len <= kMaxPrefillBlocks * kBlock) {
       for (int32_t r : bh.dec_rows) row_blocks(r);
     } else {
-      for (int r = 0; r < R; ++r) row_blocks(r);
+      for (int r = 0; r < R; ++r) {
+        row_blocks(r);
+        // a further row of a sequence walks the blocks of the row before it
+        if (r > 0 && bh.row_seq[r] == bh.row_seq[r - 1]) blk_again += bh.pos[r - 1] / kBlock + 1;
+      }
     }
   }
+  // KV that a launch reads once is loaded non-temporally, KV that its rows
+  // share with ordinary loads, which leave it in the caches for the next row.
+  // The line lies at half of the blocks.  Passes of two layers, non-temporal
+  // and ordinary: no block read again, 3B 200 rows of 1,000-3,000 tokens
+  // 1,603 and 1,769 us; a quarter, 64 rows behind one prefix (key 4 at 0) 336
+  // and 350; half, 319 and 311; three quarters, 291 and 251; nearly all, 256
+  // prompt rows behind 8,208 tokens 2,362 and 1,396.
+  aa.kv_once = 2 * blk_again < blk_sum ? 1 : 0;
   aa.bps = h.attn_bps > 0 ? h.attn_bps : attn_auto_bps(R, c.n_kv_heads);
   // 128..255 (row, KV head) pairs whose walks are within 20% of each other:
   // one split per pair (no merge, and the items are balanced already); a

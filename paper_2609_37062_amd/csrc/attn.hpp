@@ -31,6 +31,7 @@ struct AttnArgs {
   // routed layer (nullable): per row 1 RUN, 0 Project-Only; a Project-Only
   // row reads no KV and its attention output is zero (Algorithm 1)
   const uint8_t* run_mask;
+  int kv_once;  // 1: most KV blocks of the launch are read by one row only (non-temporal loads)
 };
 
 // Causal attention of prefill rows (see k_attn_prefill).

@@ -212,7 +212,7 @@ __device__ __forceinline__ void pair_pv(u32x4 (&vt)[D / 16], int t0, int t_end, 
 // FOLD2: a wave loads two shared-prefix partials before folding either (one
 // round trip per two; 186 instead of 167 registers at head_dim 128), for
 // passes with more prefix partials per row than waves.
-template <int D, bool WT, int NW, bool FOLD2 = false>
+template <int D, bool WT, int NW, bool FOLD2 = false, bool NTKV = true>
 __device__ __forceinline__ void attn_unit(const AttnArgs& a, int row, int hk, int split, AttnLds<D, NW>& sm) {
   constexpr int KC = D / 32;  // K chunks (1 KiB) per block
   constexpr int VC = D / 16;  // V chunks (512 B) per block
@@ -275,11 +275,12 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int row, int hk, in
 
   // K and V operands of blocks 2p, 2p + 1 of this wave's range (a block past
   // the range: its last block again, whose keys the step then masks).  Every
-  // load takes whole 128-byte lines (the pool's order of tokens), and a pass
-  // reads them once: non-temporal.  With half lines per load (8-byte V
-  // pieces) non-temporal loads fetched lines twice: 8B at 37 rows of
+  // load takes whole 128-byte lines (the pool's order of tokens); NTKV: what
+  // the launch reads once is loaded non-temporally.  With half lines per load
+  // (8-byte V pieces) non-temporal loads fetched lines twice: 8B at 37 rows of
   // 100-6,000 tokens 989 us ordinary, 1,013 non-temporal, 935 with whole
   // lines; 128 rows 1,089, 1,049, 1,029.
+  auto kv = [](const u32x4* p) { return NTKV ? __builtin_nontemporal_load(p) : *p; };
   auto pair_blocks = [&](int p, int cnt, int w_lo, size_t& bA, size_t& bB) {
     bA = static_cast<size_t>(sm.tbl[w_lo + min(2 * p, cnt - 1)]);
     bB = static_cast<size_t>(sm.tbl[w_lo + min(2 * p + 1, cnt - 1)]);
@@ -291,8 +292,8 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int row, int hk, in
     const int k0 = pair_k_index(lane, 0), k1 = pair_k_index(lane, 1);
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      kg[0][c] = __builtin_nontemporal_load(kp + c * 64 + k0);
-      kg[1][c] = __builtin_nontemporal_load(kp + c * 64 + k1);
+      kg[0][c] = kv(kp + c * 64 + k0);
+      kg[1][c] = kv(kp + c * 64 + k1);
     }
   };
   auto load_v = [&](u32x4 (&vt)[VC], int p, int cnt, int w_lo) {
@@ -301,7 +302,7 @@ __device__ __forceinline__ void attn_unit(const AttnArgs& a, int row, int hk, in
     const u32x4* vp =
         reinterpret_cast<const u32x4*>(vbase + (pair_v_block(lane) ? bB : bA) * kv_stride) + pair_v_index(lane);
 #pragma unroll
-    for (int c = 0; c < VC; ++c) vt[c] = __builtin_nontemporal_load(vp + c * 32);
+    for (int c = 0; c < VC; ++c) vt[c] = kv(vp + c * 32);
   };
 
   __syncthreads();  // sm.tbl

@@ -31,26 +31,31 @@ constexpr int kPreTiles = kPreCols / 16;   // 16-column tiles (one wave each) of
 // one head each of every (row, split) at 8 KV heads; with fewer heads the
 // split is turned by the row, so an XCD does not keep one split of all rows.
 // 8B at 37 rows of 100 to 6,000 tokens (four splits): 861 -> 820 us a pass.
-template <int D, bool FOLD2>
+template <int D, bool FOLD2, bool NTKV>
 __global__ __launch_bounds__(64 * kAttnWaves) void k_attn_decode(AttnArgs a) {
   __shared__ AttnLds<D, kAttnWaves> sm;
   const int split = (blockIdx.y + blockIdx.z) % gridDim.y;
-  attn_unit<D, false, kAttnWaves, FOLD2>(
+  attn_unit<D, false, kAttnWaves, FOLD2, NTKV>(
       a, a.rows != nullptr ? a.rows[blockIdx.z] : static_cast<int>(blockIdx.z), blockIdx.x, split, sm);
 }
 
-template <int D, bool FOLD2>
+template <int D, bool FOLD2, bool NTKV>
 static void launch_decode_k(const AttnArgs& a, dim3 grid, hipStream_t s, const LaunchEvents& ev) {
   if (ev.start != nullptr || ev.stop != nullptr)  // events bound to this dispatch
-    hipExtLaunchKernelGGL((k_attn_decode<D, FOLD2>), grid, dim3(64 * kAttnWaves), 0u, s, ev.start, ev.stop, 0u, a);
+    hipExtLaunchKernelGGL((k_attn_decode<D, FOLD2, NTKV>), grid, dim3(64 * kAttnWaves), 0u, s, ev.start, ev.stop, 0u, a);
   else
-    hipLaunchKernelGGL((k_attn_decode<D, FOLD2>), grid, dim3(64 * kAttnWaves), 0, s, a);
+    hipLaunchKernelGGL((k_attn_decode<D, FOLD2, NTKV>), grid, dim3(64 * kAttnWaves), 0, s, a);
 }
 
 template <int D>
 static void launch_decode_d(const AttnArgs& a, dim3 grid, bool fold2, hipStream_t s, const LaunchEvents& ev) {
-  if (fold2) launch_decode_k<D, true>(a, grid, s, ev);
-  else launch_decode_k<D, false>(a, grid, s, ev);
+  if (a.kv_once != 0) {
+    if (fold2) launch_decode_k<D, true, true>(a, grid, s, ev);
+    else launch_decode_k<D, false, true>(a, grid, s, ev);
+  } else {
+    if (fold2) launch_decode_k<D, true, false>(a, grid, s, ev);
+    else launch_decode_k<D, false, false>(a, grid, s, ev);
+  }
 }
 
 hipError_t launch_attn_decode(const AttnArgs& a, int n_rows, int grid_splits, int max_pfx_splits, hipStream_t s,

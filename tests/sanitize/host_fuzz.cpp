@@ -69,6 +69,30 @@ static void check_batch(const BlockAllocator& a, const std::vector<int64_t>& seq
   }
 }
 
+// What count_reread_blocks may say of one-row walks: no more than the blocks
+// walked beyond the distinct ones, and no less than every group's prefix for
+// each member but one; after the prefixes, no more than what is left.
+static void check_reread(const BatchHost& b, int32_t block) {
+  std::set<int32_t> all, own;
+  int64_t n_all = 0, n_own = 0, in_groups = 0;
+  for (int32_t i = 0; i < b.n_seqs; ++i) {
+    const int32_t r = b.cu_q[i];
+    if (b.cu_q[i + 1] - r != 1) continue;
+    for (int32_t k = 0; k < (b.kv_len[i] + block - 1) / block; ++k) {
+      const int32_t id = b.block_table[static_cast<size_t>(i) * b.max_blocks + k];
+      all.insert(id);
+      ++n_all;
+      if (k < b.pfx_blocks[r]) continue;
+      own.insert(id);
+      ++n_own;
+    }
+  }
+  for (int32_t g = 0; g < b.n_groups(); ++g) in_groups += static_cast<int64_t>(b.grp_info[4 * g + 1] - 1) * b.grp_info[4 * g + 2];
+  CHECK(b.reread_all >= in_groups && b.reread_all <= n_all - static_cast<int64_t>(all.size()));
+  CHECK(b.reread_own >= 0 && b.reread_own <= n_own - static_cast<int64_t>(own.size()));
+  CHECK(b.n_groups() > 0 || b.reread_own == b.reread_all);
+}
+
 static void check_prefixes(const BatchHost& b, int32_t block) {
   const int32_t ng = b.n_groups();
   for (int32_t g = 0; g < ng; ++g) {
@@ -179,6 +203,7 @@ int main(int argc, char** argv) {
         CHECK(rc == kOk);
         check_batch(a, seqs, q, b);
         for (int32_t r = 0; r < b.n_rows; ++r) CHECK(b.slot[r] == reserved[r]);
+        check_reread(b, 16);
         bool decode = true;
         for (int32_t x : q) decode = decode && x == 1;
         ++n_passes;

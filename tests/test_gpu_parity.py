@@ -4,6 +4,7 @@ Every device call goes through the C ABI (paper_2609_37062_amd.vsk); the
 oracle is the float64 CPU statement in oracle/.
 """
 import copy
+import dataclasses
 
 import numpy as np
 import pytest
@@ -424,6 +425,43 @@ def test_mid_chunked_prefill_with_context(prefill_kernel):
     st, out, kv, sub, idx = _check(w, lg, ids)
     assert_kv_layer_local(d, w)
     print(st)
+
+
+@pytest.mark.parametrize("kind", ["decode", "chunk"])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("own", [30, 700])
+def test_shared_blocks_equal_copies(kind, head_dim, own):
+    """Rows behind one common prefix that is not folded (key 4 at 0, or decode
+    rows beside a prompt) read its blocks many times, with ordinary loads where
+    they are at least half of all blocks (30 own tokens) and non-temporal ones
+    where they are less (700): bit for bit the same pass as with a copy of the
+    prefix per sequence, where no block is read twice."""
+    from paper_2609_37062_amd.runner import DeviceRun
+    model = dataclasses.replace(MID, name=f"mid-hd{head_dim}", head_dim=head_dim)
+    prefix, n = 320, 6
+    rng = np.random.default_rng(own + head_dim)
+    ctx = [prefix + own + int(x) for x in rng.integers(0, 20, size=n)]
+    got = []
+    for shared in (True, False):
+        perm = [int(b) for b in np.random.default_rng(3).permutation(600)]
+        take = lambda tokens: [perm.pop() for _ in range((tokens + 15) // 16)]  # noqa: E731
+        seqs = [SeqSpec(0, 21, [], [])] if kind == "chunk" else []
+        common = take(prefix)
+        for i, c in enumerate(ctx):
+            seqs.append(SeqSpec(c, 1, (common if shared else take(prefix)) + take(c + 1 - prefix),
+                                [(0, prefix, 1000), (prefix, c - prefix, i)]))
+        tokens = np.random.default_rng(4).integers(0, model.vocab, size=sum(q.q_len for q in seqs)).astype(np.int32)
+        w = Workload(0, f"copies-{kind}-{head_dim}-{own}-{shared}", model, seqs, 600, tokens, 6)
+        print(f"[gpu] {w.name}", flush=True)
+        d = DeviceRun(w, poison_pool=True)
+        d.eng.set_tuning(4, 0)
+        d.step()
+        got.append(d.results())
+        if shared:
+            _check(w, *got[0])
+        d.release()
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
 
 
 def test_replay_is_idempotent_and_deterministic():
