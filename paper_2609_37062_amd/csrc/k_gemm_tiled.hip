@@ -73,10 +73,10 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   constexpr int kLead = kBuf - 1;          // chunks copied ahead
   constexpr int kStep = MG + TN;           // 1 KiB fragments per K step
   constexpr int kPieces = kChunk * kStep;  // and per chunk
-  constexpr int kCopies = (kPieces + 7) / 8;  // copies per wave and chunk, one fewer for waves kFull..
-  constexpr int kFull = kPieces - 8 * (kCopies - 1);
-  constexpr int XB = (MGW + 1) / 2;        // row groups of the first half step
-  static_assert(MG % WM == 0 && kBuf >= 2 && (kLead - 1) * kCopies <= 63, "outstanding loads beyond the wait counter");
+  constexpr int kCopies = kPieces / 8;     // copies per wave and chunk
+  constexpr int XB = MGW / 2;              // row groups of a half step
+  static_assert(kPieces % 8 == 0 && MG % WM == 0 && MGW % 2 == 0, "pieces and row groups in equal shares");
+  static_assert(kBuf >= 2 && (kLead - 1) * kCopies <= 63, "outstanding loads beyond the wait counter");
   extern __shared__ __align__(16) unsigned char smem[];  // [kBuf][kChunk][MG X pieces, TN W pieces][1 KiB]
   __shared__ float s_amv[EPI == EPI_LOGITS ? WN : 1][MG][16];
   __shared__ int s_ami[EPI == EPI_LOGITS ? WN : 1][MG][16];
@@ -122,7 +122,6 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
 #pragma unroll
     for (int p = 0; p < kCopies; ++p) {
       const int pc = w + 8 * p;
-      if (p + 1 == kCopies && kFull != 8 && w >= kFull) continue;  // (uniform)
       const int st = pc / kStep, q = pc % kStep;
       if (q < MG)
         lds_copy16<false>(a.X + (static_cast<size_t>(kt + st) * a.Rg + min(q, a.Rg - 1)) * 64, voff, dst + p * 8192);
@@ -134,8 +133,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   };
   // wait until this wave's copies of all but the newest kLead - 1 chunks have landed
   auto wait_copies = [&]() {
-    if (kFull == 8 || w < kFull) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kLead - 1) * kCopies) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kLead - 1) * (kCopies - 1)) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kLead - 1) * kCopies) : "memory");
   };
   const u32x4* xs = reinterpret_cast<const u32x4*>(smem) + wm * MGW * 64 + lane;
   const u32x4* ws = reinterpret_cast<const u32x4*>(smem) + (MG + wn * NT) * 64 + lane;
@@ -145,8 +143,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
     constexpr int h = decltype(h_c)::value;
     const u32x4* p = xs + ((c % kBuf) * kPieces + st * kStep + h * XB) * 64;
 #pragma unroll
-    for (int g = 0; g < XB; ++g)
-      if (h * XB + g < MGW) r[g] = p[g * 64];
+    for (int g = 0; g < XB; ++g) r[g] = p[g * 64];
   };
   auto wread = [&](u32x4 (&r)[NT], int c, int st) {
     const u32x4* p = ws + ((c % kBuf) * kPieces + st * kStep) * 64;
@@ -156,11 +153,9 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   auto mma = [&](f32x4 (&acc)[NT][MGW], const u32x4 (&fw)[NT], const u32x4 (&r)[XB], auto h_c) {
     constexpr int h = decltype(h_c)::value;
 #pragma unroll
-    for (int g = 0; g < XB; ++g) {
-      if (h * XB + g >= MGW) continue;
+    for (int g = 0; g < XB; ++g)
 #pragma unroll
       for (int j = 0; j < NT; ++j) acc[j][h * XB + g] = mfma_16x16x32(fw[j], r[g], acc[j][h * XB + g]);
-    }
   };
   constexpr auto kH0 = std::integral_constant<int, 0>{};
   constexpr auto kH1 = std::integral_constant<int, 1>{};
