@@ -72,9 +72,6 @@ WsLayout ws_layout(const vsk_model_cfg& c, int32_t max_rows, int32_t max_seqs, i
   const int G = c.n_q_heads / c.n_kv_heads;
   size_t o = 0;
   w.x = o; o = align_up(o + static_cast<size_t>(max_rows) * H * 4);
-  // (two unused regions, here and after ssq: a workspace keeps its size, and
-  // vsk_decode_step_scratch the batches it takes)
-  o = align_up(o + static_cast<size_t>(max_rows) * H * 4);
   w.fa = o; o = align_up(o + Rp * Nq * 2);
   w.fb = o; o = align_up(o + Rp * H * 2);
   w.fc = o; o = align_up(o + Rp * F * 2);
@@ -85,7 +82,6 @@ WsLayout ws_layout(const vsk_model_cfg& c, int32_t max_rows, int32_t max_seqs, i
   w.att_cnt = o; o = align_up(o + rh * 4);  // zeroed at init, left zero by every pass
   // x^2 partials: at most one per 16 columns of the hidden size, per row
   w.ssq = o; o = align_up(o + (H / 16) * static_cast<size_t>(max_rows) * 8);
-  o = align_up(o + (H / 16) * static_cast<size_t>(max_rows) * 8);
   // residual projections with K split over workgroups: one product per split
   // and row (and the QKV projection's, N = Nq + 2 Nkv); row-tiled passes with
   // few workgroups split too

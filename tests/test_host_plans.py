@@ -1,11 +1,11 @@
-"""The projection planner of the built library (plan_gemm), called on the CPU:
-what a forced tile height (tuning key 10) gives over the sizes it is accepted
-for."""
+"""Plans and layouts of the built library, computed on the CPU: the projection
+planner (plan_gemm) and the workspace."""
 import ctypes
 
 import pytest
 
 from paper_2609_37062_amd import vsk
+from workloads.configs import M8B
 
 RESID, QKV, SWIGLU, LOGITS = range(4)
 
@@ -42,3 +42,22 @@ def test_automatic_gate_up_workgroups(N, K, rows, tiles):
     assert p.nt * p.wn == tiles
     if tiles < 16:
         assert p.mg == 8
+
+
+@pytest.mark.parametrize("rows,kv", [(256, 6001), (2080, 2048), (777, 777)])
+def test_workspace_holds_what_a_pass_uses(rows, kv):
+    """A workspace is the pass's buffers and their alignment, nothing beside them."""
+    m = M8B
+    splits = -(-(-(-kv // 16)) // 8) + 16                    # 8-block splits and prefix splits
+    qkv = m.q_dim + 2 * m.kv_dim
+    per_row = (4 * m.hidden                                  # residual
+               + 2 * m.q_dim                                 # q
+               + splits * m.n_q_heads * (4 * m.head_dim + 8) + 4 * m.n_kv_heads  # attention partials, arrivals
+               + m.hidden // 16 * 8                          # sums of x^2
+               + 8 * 4 * max(m.hidden, qkv)                  # products of K splits
+               + m.vocab // 16 * 8)                          # argmax partials
+    per_padded_row = 2 * m.q_dim + 2 * m.hidden + 2 * m.ffn  # projection inputs
+    need = rows * per_row + -(-rows // 16) * 16 * per_padded_row
+    e = vsk.Engine(m)
+    assert need <= e.workspace_bytes(rows, 1, kv) <= need + 11 * 256
+    e.close()
