@@ -121,11 +121,12 @@ def test_mid_residual_k_splits(B, target):
     print(st)
 
 
-# (model, rows, target) -> K splits of QKV: MID 40/4096 -> 2; WIDE at 3 row
-# groups (48 N groups) 0 (192) -> 4, 240 -> 5; at 7 (24 N groups) 0 -> 8,
-# 64 -> 3
+# (model, rows, target) -> K splits of QKV (test_host_plans.py pins them): MID
+# 40/4096 -> 2; WIDE at 3 row groups 0 (256) -> 5, 192 -> 4; at 7 row groups
+# 0 (192) -> 8, 64 -> 3, 128 -> 6, 168 -> 7
 @pytest.mark.parametrize("cfg,B,target", [("mid", 40, 4096), ("mid", 100, -1), ("wide", 40, -1), ("wide", 40, 0),
-                                          ("wide", 40, 240), ("wide", 100, 0), ("wide", 100, 64)])
+                                          ("wide", 40, 192), ("wide", 100, 0), ("wide", 100, 64), ("wide", 100, 128),
+                                          ("wide", 100, 168)])
 def test_mid_qkv_k_splits(cfg, B, target):
     """QKV with K split over workgroups (the splits' products added in split
     order by the kernel that applies rotary and writes q and the KV slots):

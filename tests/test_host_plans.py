@@ -44,6 +44,15 @@ def test_automatic_gate_up_workgroups(N, K, rows, tiles):
         assert p.mg == 8
 
 
+@pytest.mark.parametrize("N,K,rows,target,splits", [
+    (1536, 512, 40, 4096, 2), (3072, 2048, 40, 256, 5), (3072, 2048, 40, 192, 4), (3072, 2048, 100, 192, 8),
+    (3072, 2048, 100, 64, 3), (3072, 2048, 100, 128, 6), (3072, 2048, 100, 168, 7)])
+def test_qkv_k_splits(N, K, rows, target, splits):
+    """The split counts that the GPU tests of the QKV projection stand for: 2 to
+    8, one for each count the reduction is compiled for."""
+    assert plan(N, K, rows, RESID, resid_target=target).ksplit == splits
+
+
 @pytest.mark.parametrize("rows,kv", [(256, 6001), (2080, 2048), (777, 777)])
 def test_workspace_holds_what_a_pass_uses(rows, kv):
     """A workspace is the pass's buffers and their alignment, nothing beside them."""
