@@ -90,7 +90,9 @@ typedef struct vsk_layer_weights {
 } vsk_layer_weights;
 
 /* Bytes of the packed weight buffer (all layers, embedding, lm_head, norms,
- * rotary table). */
+ * rotary table).  Matrices whose K is a multiple of 2048 are stored with 4
+ * KiB between rows of tiles: 3% more than their weights at K = 4096, 6% at
+ * 2048. */
 size_t vsk_packed_weight_bytes(const vsk_model_cfg* cfg);
 /* Bind a caller-owned device buffer of at least vsk_packed_weight_bytes(). */
 int vsk_weights_bind(vsk_handle* h, void* packed_dev, size_t bytes);
@@ -393,20 +395,23 @@ int vsk_set_probe(vsk_handle* h, int32_t which, void* const* begin_events,
  *        tiles (two per wave), residual projections and QKV over eight with
  *        K split over workgroups (QKV unsplit: two).  More than 128 rows
  *        take the staging with the eight waves side by side (16 tiles, 8
- *        for QKV).  1 one column of K-split waves, one tile, every
+ *        for QKV).  From 65 rows on, gate/up and lm_head of so few columns
+ *        that those tiles leave at least half of the compute units idle take
+ *        8, 4 or 2 tiles.  1 one column of K-split waves, one tile, every
  *        projection; 2 the same with two tiles; 3 the 2 x 2 grid everywhere;
  *        4 staging with four tiles (two for QKV) everywhere, residual
  *        projections with K split over workgroups; 5 for 65 rows or more
- *        (QKV aside) staging with eight tiles, everything else shape 3; 6 the
- *        default's staging for every projection but the residual ones,
+ *        (QKV aside) staging with eight tiles, everything else shape 3; 6
+ *        staging for every projection but the residual ones of 17..64 rows,
  *        whatever the row tiling.
  * key 4: shared prefixes of a decode pass (vsk_batch_prefix_info): 1 (the
  *        default) reads each group's prefix blocks once for the group, 0 reads
  *        them once per sequence.
  * key 5: residual projections (O, down) of passes of at most 128 rows: the
  *        workgroup count their K split aims for (1..4096); 0 (the default):
- *        at most 256 workgroups at 17..64 rows, 384 at 65..128, 192 for the down projection at 1..16 rows (two tiles
- *        per workgroup), no split for O at 1..16 rows (measured no faster);
+ *        at most 256 workgroups at 17..64 rows, 384 at 65..128, 192 for the
+ *        down projection at 1..16 rows (two tiles per workgroup), no split
+ *        for O at 1..16 rows (measured no faster);
  *        -1: no split.  Split products are added to the residual in
  *        split order by the RMSNorm that follows.  Passes of more than 128
  *        rows whose residual projections have at most 128 workgroups (N
@@ -418,8 +423,9 @@ int vsk_set_probe(vsk_handle* h, int32_t which, void* const* begin_events,
  *        work item per row, as for decode rows.
  * key 7: the QKV projection of passes of 17..128 rows: the workgroup count
  *        its K split aims for (1..4096); 0 (the default): 256 at 17..64 rows,
- *        192 above; -1: no split (the epilogue in the projection).  Split products are added in split order by a kernel
- *        that then applies rotary and writes q and the KV slots.  Passes of
+ *        192 above; -1: no split (the epilogue in the projection).  Split
+ *        products are added in split order by a kernel that then applies
+ *        rotary and writes q and the KV slots.  Passes of
  *        more than 128 rows split QKV the same way when the residual
  *        layout would give it at most 128 workgroups (within 256 after the
  *        split), unless the key is -1.
@@ -435,7 +441,8 @@ int vsk_set_probe(vsk_handle* h, int32_t which, void* const* begin_events,
  *        projections: 6 or 7) where the launch then takes fewer rounds x
  *        tile height than at 8 (one workgroup per compute unit, 256 per
  *        round; launches that split K keep 8), else 8; 6, 7, 8 or 11 force
- *        that height (11 gives 8 for the residual projections). */
+ *        that height (11 gives 8 for the residual projections) and, for
+ *        gate/up, the 16 tiles of key 3. */
 int vsk_set_tuning(vsk_handle* h, int32_t key, int32_t value);
 
 /* Inspection: copy the fp32 residual stream x [n_rows][hidden] left in the

@@ -1063,7 +1063,10 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
   // fewer pairs keep it for the parallelism.  Nor is any walk cut that is no
   // longer than what each of the kAttnSlots workgroups in flight has to walk
   // in all (8B, 100 rows of 1,500 to 2,500 tokens: 1,202 us for four layers at
-  // 96 blocks a split, 1,114 uncut).
+  // 96 blocks a split, 1,114 uncut).  Rows that a route tape makes Project-Only
+  // count too, the tape being on the device: with nine in ten of them uncut
+  // walks lose (128 rows of 4,000 to 7,900 tokens, two layers: 940 us uncut,
+  // 899 cut; with half of them 1,070 and 1,084).
   const int pairs = n_dec * c.n_kv_heads;
   if (h.attn_bps == 0 && n_dec > 0 && ((pairs >= 128 && pairs < 256 && 5 * blk_min >= 4 * blk_max) ||
                                        blk_sum * c.n_kv_heads >= static_cast<int64_t>(kAttnSlots) * blk_max))
@@ -1119,10 +1122,10 @@ hipError_t run_pass(Handle& h, const PassArgs& pa, hipStream_t s) {
 
   const int rt = h.resid_target;  // -1 no split, 0 the layout's default, else the target
   const GemmPlan p_qkv = plan_gemm(Nq + 2 * Nkv, H, R, EPI_QKV, h.gemm_shape, 0, h.row_tile);
-  // QKV of one row tile at 4 or 8 row groups: K split over workgroups of
-  // the residual projections' layout (4 or 8 N tiles each instead of 2, so
-  // each activation chunk staged in LDS feeds two or four times the weight
-  // bytes), the products added by k_qkv_reduce, which applies the epilogue
+  // QKV of more than 16 rows: K split over workgroups of the residual
+  // projections' layout (at 8 row groups 8 N tiles each instead of 2, so each
+  // activation chunk staged in LDS feeds four times the weight bytes), the
+  // products added by k_qkv_reduce, which applies the epilogue
   GemmPlan p_qkv_split;
   if (h.qkv_target >= 0 && p_qkv.mg >= 4)
     p_qkv_split = plan_gemm(Nq + 2 * Nkv, H, R, EPI_RESID, h.gemm_shape,

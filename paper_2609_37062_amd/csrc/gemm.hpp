@@ -45,16 +45,16 @@ constexpr int kMaxResidSplits = 8;
 constexpr int kResidTargetWgs = 0;  // default split-K target of the residual projections (0: no split)
 constexpr int kTiledGroups = 4;       // 16-row groups of a k_gemm_tiled launch
 constexpr int kTiledTargetWgs = 256;  // default split-K target at 17..64 rows: one round of compute units
-constexpr int kQkvTargetWgs = 192;  // default split-K target of QKV at 4..8 row groups
+constexpr int kQkvTargetWgs = 192;  // and of QKV in the layouts of k_gemm
 constexpr int kRowTiledSplitBelow = 128;  // row-tiled residual projections split K at or below these workgroups
 constexpr int kRowTiledTarget = 256;      // into as many splits as stay within this many workgroups
 constexpr int kComputeUnits = 256;        // MI355X: 8 XCDs x 32 compute units
 
 // shape: launch shape for 4 or 8 row groups (0 default; see k_gemm.hip)
 // resid_target: workgroups a residual projection's K split aims for (-1: no
-// split; 0: the layout's default -- 192 or 384 with X in LDS, 192 for the
-// two-tile layout of the down projection at <= 16 rows, else
-// kResidTargetWgs)
+// split; 0: the layout's default -- kTiledTargetWgs in k_gemm_tiled, 384 (192
+// at 4 row groups) with X in LDS, 192 for the two-tile layout of the down
+// projection at <= 16 rows, else kResidTargetWgs)
 // row_tile: 16-row groups per tile of a row-tiled projection other than the
 // lm_head (0: chosen from the launch rounds; 6, 7, 8 or 11: that height)
 GemmPlan plan_gemm(int N, int K, int R, int epi, int shape = 0, int resid_target = 0, int row_tile = 0);

@@ -36,7 +36,10 @@ inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a
 // channels: a pure stream of 28672 x 4096 43.3 us without the four, 37.5 with
 // them, of 128256 x 4096 168 and 153 (two more 38.1 / 157, eight 37.7 / 153);
 // gate/up of that size at 16 rows 49.1 and 41.3, at 37 rows 41.5 and 40.8, at
-// 128 the same.  At K = 3072 (96 KiB rows) they change nothing.
+// 128 the same.  At K = 3072 (96 KiB rows) they change nothing.  The cost: 3%
+// more memory at K = 4096, 6% at 2048, and 1-2% in the persistent step, whose
+// workgroups each walk one run of rows of tiles (8B, 4 layers, 4 rows: 501 us
+// without, 511 with them; the default path 431 and 400).
 __host__ __device__ inline int w_stride(int Kt) { return Kt % 64 == 0 ? Kt + 4 : Kt; }
 inline size_t w_bytes(size_t N, size_t K) { return N / 16 * w_stride(static_cast<int>(K / 32)) * 1024; }
 
@@ -186,7 +189,7 @@ struct Handle {
   int shared_prefix = 1;  // read shared prefixes once per group (decode passes)
   int pfx_target = 192;   // workgroups the shared-prefix work items of a pass aim for
   int resid_target = 0;   // residual projections: split-K workgroup target (0 default, -1 no split)
-  int qkv_target = 0;     // QKV at 4..8 row groups: split-K workgroup target (0 default, -1 no split)
+  int qkv_target = 0;     // QKV of more than 16 rows: split-K workgroup target (0 default, -1 no split)
   int prefill_attn = 1;   // prefill rows through the causal multi-row kernel (0: one row per work item)
   int xcd_remap = 1;      // row-tiled projections: XCD-aware workgroup order (0: dispatch order)
   int row_tile = 0;       // row-tiled projections: 16-row groups per tile (0 auto; 6, 7, 8 or 11)

@@ -30,7 +30,10 @@ constexpr int kPreTiles = kPreCols / 16;   // 16-column tiles (one wave each) of
 // XCDs and its remainder on the odd ones.  With the head fastest the XCDs get
 // one head each of every (row, split) at 8 KV heads; with fewer heads the
 // split is turned by the row, so an XCD does not keep one split of all rows.
-// 8B at 37 rows of 100 to 6,000 tokens (four splits): 861 -> 820 us a pass.
+// 8B at 37 rows of 100 to 6,000 tokens (four splits): 861 -> 820 us a pass;
+// two layers of hidden 3072, split not turned and turned: 2 KV heads, 37 rows
+// of 100 to 6,000 tokens 216 -> 203, 16 of 2,000 to 4,000 168 -> 161; 4 heads,
+// 37 rows 264 -> 256, 100 rows of 1,500 to 2,500 396 -> 375.
 template <int D, bool FOLD2, bool NTKV>
 __global__ __launch_bounds__(64 * kAttnWaves) void k_attn_decode(AttnArgs a) {
   __shared__ AttnLds<D, kAttnWaves> sm;

@@ -506,10 +506,13 @@ static hipError_t launch_ntw(const GemmArgs& a_in, int m_tiles, int ksplit, hipS
 // stream from displacing what the L2 holds (a pure stream of 235 MB in this
 // order 46.6 -> 43.2 us; the batch-1 pass of four 3B layers and the head 407
 // -> 371 us, batch 128 of four 8B layers 1135 -> 1089).  Row tiles share
-// weight tiles through the L2: ordinary loads.  So do residual and QKV
-// projections of 65 to 128 rows below 64 MiB of weights (QKV at 100 and 128
-// rows of the 3B and 8B shapes 14.8 and 20.0 us non-temporal, 13.1 and 18.9
-// not; O and down of the 3B 15.0 and 14.2; with the 8B down 22.2 and 22.7).
+// weight tiles through the L2: ordinary loads.  So do, for a reason that is not
+// known, residual projections and QKV with K split over workgroups at 65 to 128
+// rows below 64 MiB of weights.  Passes of three layers at 100 rows, non-temporal
+// everywhere / this rule / ordinary for all of them: hidden 2048 (the largest
+// 32 MiB) 284 / 267 / 267 us, 3072 (48) 338 / 329 / 328, 4096 (down 112) 458 /
+// 445 / 461, 5120 (QKV 70, down 135) 583 / 574 / 595, 8192 (O 128 to down 448)
+// 1,263 / 1,262 / 1,305; at 65 and 128 rows the same order.
 template <int MG, int NT, int WN, int WK, int PF, int EPI, bool XL = false>
 static hipError_t launch_cfg(const GemmArgs& a, int m_tiles, int ksplit, hipStream_t s, const LaunchEvents& ev) {
   constexpr bool kOneTile = MG == 1 || MG == 4;    // never row-tiled
@@ -527,20 +530,20 @@ static hipError_t launch_cfg(const GemmArgs& a, int m_tiles, int ksplit, hipStre
 //  pair    two N tiles per wave, 4 K steps in flight (QKV, gate/up);
 //  wide    four N tiles per wave (lm_head).
 // For 2..4 row groups the default (shape 0) is k_gemm_tiled; the layouts of 4
-// row groups here are what shapes 1..6 select.  For 5..8 row groups (and
-// shape 6 at 4) it is, with one row tile: X staged
-// in LDS by a ninth wave for gate/up (four N tiles; at 8 row groups eight,
-// two per wave) and lm_head (sixteen, two per wave, the eight waves side by
-// side), for the residual projections and QKV the four-tile (4 row groups)
-// or eight-tile (8) LDS layout with K split over workgroups (unsplit QKV:
-// two N tiles per workgroup).  A row-tiled pass (more than 128 rows) takes
-// the LDS layout with the eight waves side by side (16 N tiles; 8 for QKV).
+// row groups here are what shapes 1..6 select.  For 5..8 row groups it is,
+// with one row tile: X staged in LDS by a ninth wave for gate/up and the
+// residual projections (eight N tiles, two per wave; the residual ones with K
+// split over workgroups, QKV split the same way) and lm_head (sixteen, two per
+// wave, the eight waves side by side); unsplit QKV takes two N tiles per
+// workgroup.  A row-tiled pass (more than 128 rows) takes the LDS layout with
+// the eight waves side by side (16 N tiles; 8 for QKV).  Gate/up and lm_head
+// of few columns take 8, 4 or 2 N tiles (plan_gemm).
 // Shape 1 takes one N tile per wave column everywhere, shape 2 two, shape 3
 // is a 2 x 2 wave grid over four N tiles, shape 4 stages X in LDS for four N
-// tiles (two for QKV) everywhere, shape 5 for eight (two per wave) at 8 row
-// groups with QKV and 4 row groups on the 2 x 2 grid, shape 6 the default's
-// LDS layouts for every projection but the residual ones, whatever the row
-// tiling.
+// tiles (two for QKV; sixteen for lm_head at 4 row groups), shape 5 for eight
+// (two per wave) at 8 row groups with QKV and 4 row groups on the 2 x 2 grid,
+// shape 6 is the LDS layouts for every projection but the residual ones of 4
+// row groups, whatever the row tiling.
 // Row-tiled passes whose launch rounds another tile height fills better
 // than 8 row groups (see plan_gemm): staged X, the eight waves side by side,
 // as at 8 (QKV keeps one N tile per wave: two spill 147 registers in its
@@ -633,7 +636,7 @@ GemmPlan plan_gemm(int N, int K, int R, int epi, int shape, int resid_target, in
       // spare): the eight waves side by side, 16 N tiles per workgroup
       // (half the X reads per weight byte; lm_head 242 -> 222 us at batch
       // 128, the 2,080-row pass 21.0 -> 16.6 ms with QKV below)
-      if (epi == EPI_LOGITS || (epi != EPI_QKV && !one_tile)) {
+      if (epi == EPI_LOGITS || !one_tile) {
         p.wn = 8;
         wk = 1;
       }
@@ -667,17 +670,13 @@ GemmPlan plan_gemm(int N, int K, int R, int epi, int shape, int resid_target, in
       p.xl = true;
       p.wn = 8;
       wk = 1;
-    } else if (shape == 3 || shape == 5 || (auto_shape && !one_tile)) {
-      // a row-tiled pass (more than 128 rows) re-streams the weights once per
-      // row tile: there the 2 x 2 wave grid, each X chunk feeding four N
-      // tiles, is the faster default
+    } else if (shape == 3 || shape == 5) {
       p.nt = 2;
       p.wn = 2;
       wk = 2;
-    } else if (shape == 4 || ((shape == 6 || auto_shape) && epi != EPI_RESID) || auto_shape) {
-      // X in LDS: four N tiles per workgroup (two for QKV, whose N is small);
-      // the default for every projection of one row tile at 4 row groups
-      // (the residual ones with K split over workgroups)
+    } else if (auto_shape || shape == 4 || (shape == 6 && epi != EPI_RESID)) {
+      // X in LDS: four N tiles per workgroup (two for QKV, whose N is small).
+      // By default only QKV of one row tile at 8 row groups without its K split.
       p.xl = true;
       p.wn = epi == EPI_QKV ? 2 : 4;
       wk = 8 / p.wn;
@@ -730,8 +729,8 @@ GemmPlan plan_gemm(int N, int K, int R, int epi, int shape, int resid_target, in
   // a residual projection of one row tile splits K until the workgroups
   // reach resid_target, keeping at least 4 K steps per wave; k_resid_norm
   // then adds the splits' products into the residual.  With X in LDS the
-  // default target is 192 workgroups at 4 row groups (4 splits at hidden
-  // 3072) and 384 at 8 (measured best of 96-384 and 128-384).
+  // target is 384 workgroups at 8 row groups and 192 at 4 (shape 4; measured
+  // best of 128-384 and 96-384).
   const int target = resid_target < 0            ? 0
                      : resid_target > 0          ? resid_target
                      : p.xl                      ? (p.mg == 4 ? 192 : 384)

@@ -407,8 +407,9 @@ GemmPlan plan_tiled(int N, int K, int R, int epi, int target) {
     p.nt = tn / p.wn;
     p.n_groups = (N / 16 + tn - 1) / tn;
     if (epi == EPI_RESID && target > 0) {
-      // as many K splits as keep the launch within the target, of at least
-      // eight steps each, every one a whole number of chunks
+      // as many K splits as keep the launch within the target, K / splits at
+      // least eight steps, every split a whole number of chunks (the last one
+      // what is left)
       const int want = std::clamp(target / p.n_groups, 1, std::min(kMaxResidSplits, std::max(1, Kt / 8)));
       const int kc = (Kt / kChunk + want - 1) / want * kChunk;
       p.ksplit = (Kt + kc - 1) / kc;

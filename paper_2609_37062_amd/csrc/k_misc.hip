@@ -16,8 +16,7 @@ namespace vsk {
 // kXcdRows rows on, all 16 rows of a group go to one XCD (a group to each XCD
 // in turn), and its L2 completes the lines: 2,080 rows of k_rmsnorm_frags 15.1
 // -> 12.5 us, k_first_norm 21.4 -> 18.3, k_resid_norm<2> of 777 rows of 4,096
-// 15.0 -> 13.7.  (Fewer rows would
-// leave XCDs idle.)
+// 15.0 -> 13.7.  (Fewer rows would leave XCDs idle.)
 constexpr int kXcdRows = 128;
 struct RowPart {
   int row, part;
@@ -41,8 +40,7 @@ static int xcd_grid(int R, int parts) {  // (rows past R exit at once)
 // outside the table give a zero row.  The sum of squares in double, added in a
 // fixed order, the product in double and rounded once, as in k_resid_norm.
 // What bounds it is the launch: gather and norm as two kernels took 4-5 us
-// each at a few rows (12.5 and 16 for 2,080), as one 4.6-5
-// (21).
+// each at a few rows, 12.5 and 16 for 2,080; as one 4.6-5 and 18.3.
 // EMBED also clears the `n_zero` words at `zero` (a caller's arrival counters).
 template <bool EMBED>
 __global__ __launch_bounds__(1024) void k_first_norm(const void* __restrict__ src, const int32_t* __restrict__ idx,
