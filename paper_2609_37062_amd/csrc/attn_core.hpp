@@ -94,9 +94,8 @@ struct PTerms {
 // before P V); alpha rescales O.  Keys at t >= t_end do not count; with MASK
 // a key also needs t <= lim.  FULL: every key of the step counts for every
 // column of the wave, and nothing is compared.  Base 2 (sc = log2(e) /
-// sqrt(D)), the scale folded into the exponent's fma.  A column with no valid
-// key yet keeps m = -inf and contributes nothing (its exponents are taken
-// against 0, so they are -inf and not NaN).
+// sqrt(D)).  A column with no valid key yet keeps m = -inf and contributes
+// nothing (its exponents are taken against 0, so they are -inf and not NaN).
 //
 // The walk is paced by these instructions (two waves a SIMD beside 32 MFMAs a
 // step), so the step is kept short: hardware bf16 conversion, no compares in
@@ -105,11 +104,15 @@ struct PTerms {
 // tokens (3B-class layer): 289 -> 182 us; shared prefix of 64 sequences 12.9 ->
 // 10.7 us, their own keys after it 14.9 -> 13.4 us.
 //
-// The fma takes the product unrounded and mb is the maximum's product rounded,
-// so the maximum's exponent is not 0 but up to half an ulp of mb away: nothing
-// for ordinary scores, 128 (and the probabilities infinite or all flushed) at
-// 2^31.  From kRoundedScores on, where half an ulp is 1/2, the product is
-// rounded first.
+// The exponent of a key is its scaled score less the maximum's, both rounded
+// alike, so that the maximum's is 0.  A fma of the two takes the product
+// unrounded and is up to half an ulp of the maximum away: nothing for ordinary
+// scores, 128 (and the probabilities infinite or all flushed) at 2^31.  The
+// walk of prompt rows (MASK), which these instructions pace, takes it below
+// kRoundedScores, where half an ulp is at most 1/4 (later chunk of 1,000 rows,
+// four layers: 1,862 us with fmas alone, 1,863 with them and the branch, 1,872
+// without fmas); the others, which wait for memory, never do (8B at 37 rows of
+// 100-6,000 tokens 845, 850 and 846).
 constexpr float kRoundedScores = 0x1p23f;
 template <int D, bool MASK, bool FULL>
 __device__ __forceinline__ void pair_scores(const u32x4 (&qf)[D / 32], const u32x4 (&kg)[2][D / 32], int t0,
@@ -139,7 +142,7 @@ __device__ __forceinline__ void pair_scores(const u32x4 (&qf)[D / 32], const u32
   // below 2^-126 (flushed to 0) is negligible beside the maximum's 1
   alpha = __builtin_amdgcn_exp2f(m - mb);
   float p[8], ps[2] = {0.f, 0.f};
-  if (__any(fabsf(mb) >= kRoundedScores)) {
+  if (!MASK || __builtin_expect(__any(fabsf(mb) >= kRoundedScores), 0)) {
     // both sides of the difference rounded alike, so the maximum's is 0
 #pragma clang fp contract(off)
 #pragma unroll
