@@ -100,10 +100,12 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   const int k_lo = ks * kc, k_hi = min(a.Kt, k_lo + kc);
   const int n_chunks = (k_hi - k_lo) / kChunk;
 
-  // one sum per step of a chunk, added at the end
-  f32x4 sums[kChunk][NT][MGW];
+  // one sum per step of a chunk, added at the end (the head's logits, rounded
+  // to bf16, keep one: so they had in the staged layout)
+  constexpr int kSums = EPI == EPI_LOGITS ? 1 : kChunk;
+  f32x4 sums[kSums][NT][MGW];
 #pragma unroll
-  for (int st = 0; st < kChunk; ++st)
+  for (int st = 0; st < kSums; ++st)
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
     if (st == 0) copy(c + kLead);
     xread(xb, c, st, kH1);
     __builtin_amdgcn_sched_barrier(0);
-    mma(sums[st], wc, xa, kH0);
+    mma(sums[st % kSums], wc, xa, kH0);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (st == kChunk - 1) {
       wait_copies();
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
       xread(xa, c, st + 1, kH0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    mma(sums[st], wc, xb, kH1);
+    mma(sums[st % kSums], wc, xb, kH1);
     __builtin_amdgcn_sched_barrier(0);
   };
   static_assert(kChunk == 2, "two weight fragment sets, one per step of a chunk");
@@ -200,10 +202,12 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tiled(GemmArgs a) {
   // the copies past the last step must land before the workgroup ends
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   f32x4 (&acc)[NT][MGW] = sums[0];
+  if constexpr (kSums > 1) {
 #pragma unroll
-  for (int j = 0; j < NT; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int g = 0; g < MGW; ++g) acc[j][g] += sums[1][j][g];
+      for (int g = 0; g < MGW; ++g) acc[j][g] += sums[1][j][g];
+  }
 
   // ---- epilogues
   if constexpr (EPI == EPI_RESID) {
