@@ -199,7 +199,7 @@ int build_batch(const BlockAllocator& a, const int64_t* seqs, const int32_t* q_l
   }
   b.pfx_blocks.assign(b.n_rows, 0);
   if (b.max_q_len == 1) find_shared_prefixes(b, bs);
-  count_reread_blocks(b, bs);
+  count_reread_blocks(a, b);
   out = std::move(b);
   return kOk;
 }
@@ -264,7 +264,8 @@ void plan_prefill_items(BatchHost& b, int32_t group_size, int32_t block) {
   std::stable_sort(b.dec_rows.begin(), b.dec_rows.end(), [&](int32_t x, int32_t y) { return walk(x) > walk(y); });
 }
 
-void count_reread_blocks(BatchHost& b, int32_t block) {
+void count_reread_blocks(const BlockAllocator& a, BatchHost& b) {
+  const int32_t block = a.block();
   std::unordered_map<int32_t, int32_t> first;  // first block of a walk -> the first sequence that starts there
   auto count = [&](bool after_prefix) {
     int64_t again = 0;
@@ -274,19 +275,19 @@ void count_reread_blocks(BatchHost& b, int32_t block) {
       if (b.cu_q[i + 1] - r != 1) continue;
       const int32_t from = after_prefix ? b.pfx_blocks[r] : 0, to = b.pos[r] / block + 1;
       const int32_t* t = b.block_table.data() + static_cast<size_t>(i) * b.max_blocks;
+      if (!a.shared(t[from])) continue;
       const auto at = first.emplace(t[from], i);
       if (at.second) continue;
       const int32_t j = at.first->second, rj = b.cu_q[j];
       const int32_t* u = b.block_table.data() + static_cast<size_t>(j) * b.max_blocks;
       if ((after_prefix ? b.pfx_blocks[rj] : 0) != from) continue;
       const int32_t end = std::min(to, b.pos[rj] / block + 1);
-      int32_t k = from;
+      int32_t k = std::max(from, std::min(b.pfx_blocks[r], b.pfx_blocks[rj]));  // (one group: the same up to there)
       while (k < end && t[k] == u[k]) ++k;
       again += k - from;
     }
     return again;
   };
-  first.reserve(b.n_seqs);
   b.reread_all = count(false);
   b.reread_own = b.n_groups() > 0 ? count(true) : b.reread_all;
 }

@@ -48,6 +48,8 @@ class BlockAllocator {
   int32_t n_blocks() const { return static_cast<int32_t>(ref_.size()); }
   int32_t block() const { return block_; }
   int32_t free_count() const { return free_count_; }
+  // more than one sequence holds block b
+  bool shared(int32_t b) const { return ref_[b] > 1; }
 
  private:
   // lowest free block id at or after `from`, or -1
@@ -100,7 +102,7 @@ void plan_prefill_items(BatchHost& b, int32_t group_size, int32_t block);
 // Count the blocks that the walks of one-row sequences read again
 // (reread_own, reread_all): a sequence against the first one whose walk starts
 // at the same block, as far as their tables agree.
-void count_reread_blocks(BatchHost& b, int32_t block);
+void count_reread_blocks(const BlockAllocator& a, BatchHost& b);
 
 // Columns (row, query head) of one shared-prefix work item: 4 tiles of 16,
 // each walked by two waves; of one prefill work item: 8 tiles of 16.
